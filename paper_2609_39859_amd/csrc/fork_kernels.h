@@ -53,6 +53,14 @@ hipError_t launch_gemm_stats(const void* hidden, const void* W, bool bf16,
                              const int32_t* rowlist, int Mh, const SampleArgs& sample,
                              const TargetArgs& target, hipStream_t stream);
 
+// The same for bf16 with 64, 128 or 256 positions per workgroup; the same
+// partials, bit for bit.  nontemporal: W is loaded past the caches (always for
+// 256 positions).
+hipError_t launch_gemm_narrow(int positions, bool nontemporal, const void* hidden, const void* W,
+                              int M, int d, int V, float4* partials, const int32_t* rowlist,
+                              int Mh, const SampleArgs& sample, const TargetArgs& target,
+                              hipStream_t stream);
+
 // Merge the partials of each position over all vocabulary tiles into the
 // per-position results (position p lands in row p, or rowlist[p] if a row
 // list is given; -1 = dropped).  lse may be null.  Positions with
