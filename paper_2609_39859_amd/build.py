@@ -18,7 +18,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libforkstep.so")
-SOURCES = ["gemm_stats.hip", "gemm_narrow.hip", "merge_select.hip", "grpo.hip", "fork_abi.hip"]
+SOURCES = ["gemm_stats.hip", "gemm_narrow.hip", "gemm_f32.hip",
+           "merge_select.hip", "grpo.hip", "fork_abi.hip"]
 PROBE_LIB = os.path.join(HERE, "libforkprobe.so")
 PROBE_SOURCES = ["peak_probe.hip"]
 ARCH = "gfx950"

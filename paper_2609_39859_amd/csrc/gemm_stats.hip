@@ -11,16 +11,18 @@
 //   m   = max_v z_v                 idx = lowest v attaining m
 //   s   = sum_v exp(z_v - m)        t   = sum_v exp(z_v - m) * (z_v - m)
 //
-// Work decomposition (gfx950 / CDNA4), common to both element types:
+// This file: the bf16 kernel with 256 positions per workgroup, and the choice
+// of the kernel of a launch.  Fewer positions per workgroup are in
+// gemm_narrow.hip, fp32 inputs in gemm_f32.hip.
+//
+// Work decomposition (gfx950 / CDNA4):
 //   * one workgroup = 256 vocabulary rows x 256 positions, 8 wave64s laid out
 //     2 (vocabulary) x 4 (positions); each wave owns 128 x 64 outputs (fp32
-//     accumulators): 8 x 4 blocks of 16 x 16 (v_mfma_f32_16x16x32_bf16) on
-//     the bf16 path, 4 x 2 blocks of 32 x 32 (v_mfma_f32_32x32x2f32) on the
-//     fp32 path;
+//     accumulators): 8 x 4 blocks of 16 x 16 (v_mfma_f32_16x16x32_bf16);
 //   * the MFMA "A" operand is W (vocabulary on the MFMA M axis) and "B" is
 //     hidden, so each lane's accumulators hold vocabulary values of whole
-//     positions: the vocabulary reduction is mostly in-lane (32 or 64 values
-//     per position), plus shuffles between the lanes holding the same
+//     positions: the vocabulary reduction is mostly in-lane (32 values per
+//     position), plus shuffles between the lanes holding the same
 //     position and one LDS exchange between the two vocabulary waves;
 //   * K is staged through LDS in 128-byte slabs per row (whole cache lines),
 //     the 16-byte chunk c of row r stored at chunk slot c ^ f(r) with
@@ -31,8 +33,8 @@
 //     stripes across all position tiles, so concurrently running workgroups
 //     share W and hidden stripes in L2.
 //
-// bf16 path (the hot one): K is fed to LDS by buffer loads that write LDS
-// directly (no register staging).  W gets a 3-slot ring (prefetched two
+// K is fed to LDS by buffer loads that write LDS directly (no register
+// staging).  W gets a 3-slot ring (prefetched two
 // stages ahead: it streams from HBM), hidden a 2-slot ring (one stage ahead:
 // it stays in the last-level cache): 5 x 32 KiB = the whole 160 KiB of LDS.
 // One barrier per 64-element K stage, placed after the first MFMAs of the
@@ -42,7 +44,6 @@
 // that no wave stalls its MFMA stream behind a burst of loads.  The 16x16x32
 // MFMA shape moves the same bytes per flop as 32x32x16 and, on gfx950,
 // sustains a higher clock under the same power limit.
-// fp32 path (small problems): register-staged double buffer.
 //
 // Drawn candidates (sampling temperature tau > 0, Section 2): for the
 // positions the caller marks, the epilogue also keeps the maximiser of the
@@ -379,114 +380,6 @@ __device__ __forceinline__ void gemm_stats_bf16_body(
   epilogue<Acc16, kMode>(acc, smem, tid, lane, wv, wp, vt, v0, pos, M, V, partials, sa, ta, ci);
 }
 
-// fp32 inputs: register-staged double buffer, two v_mfma_f32_32x32x2f32 per
-// 16-byte chunk.
-template <int kMode>
-__device__ __forceinline__ void gemm_stats_f32_body(
-    const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ W, int M, int d,
-    int V, int nvt, int npt, float4* __restrict__ partials, const int32_t* __restrict__ rowlist,
-    int Mh, const SampleArgs& sa, const TargetArgs& ta) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kOperandBytes];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wv = wave & 1;
-  const int wp = wave >> 1;
-
-  int vt, pt;
-  map_tile(blockIdx.x, nvt, npt, vt, pt);
-  const int v0 = vt * kTileV;
-  const int p0 = pt * kTileP;
-
-  const size_t row_bytes = (size_t)d * 4;
-  const int kchunks = (int)(row_bytes >> 4);
-  const int nk = (kchunks + 7) >> 3;
-
-  // Global -> LDS copy assignment: thread owns chunk c of rows r0 + 64*i.
-  const int c = tid & 7;
-  const int r0 = tid >> 3;
-  const unsigned char* ga[4];
-  const unsigned char* gb[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    // Rows past the end re-read the last row; their results are discarded.
-    const int vr = min(v0 + r0 + 64 * i, V - 1);
-    int pr = min(p0 + r0 + 64 * i, M - 1);
-    // positions without a valid row read row 0 (their results are dropped
-    // or unspecified); rows stay inside hidden
-    if (rowlist) pr = min(max(rowlist[pr], 0), Mh - 1);
-    ga[i] = W + (size_t)vr * row_bytes + (c << 4);
-    gb[i] = hidden + (size_t)pr * row_bytes + (c << 4);
-  }
-  uint4 ra[4], rb[4];
-  auto gload = [&](int kt) {
-    const bool ok = (kt * 8 + c) < kchunks;  // chunks past d are zero on both sides
-    const size_t off = (size_t)kt * kSlab;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      ra[i] = ok ? *reinterpret_cast<const uint4*>(ga[i] + off) : make_uint4(0, 0, 0, 0);
-      rb[i] = ok ? *reinterpret_cast<const uint4*>(gb[i] + off) : make_uint4(0, 0, 0, 0);
-    }
-  };
-  auto sstore = [&](int buf) {
-    unsigned char* sa = smem + (buf * 2 + 0) * kOperandBytes;
-    unsigned char* sb = smem + (buf * 2 + 1) * kOperandBytes;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      *reinterpret_cast<uint4*>(sa + lds_off(r0 + 64 * i, c)) = ra[i];
-      *reinterpret_cast<uint4*>(sb + lds_off(r0 + 64 * i, c)) = rb[i];
-    }
-  };
-
-  f32x16 acc[4][2];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  const int arow = wv * 128 + (lane & 31);
-  const int brow = wp * 64 + (lane & 31);
-  const int khalf = lane >> 5;
-
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) gload(kt + 1);
-    const unsigned char* sa = smem + (buf * 2 + 0) * kOperandBytes;
-    const unsigned char* sb = smem + (buf * 2 + 1) * kOperandBytes;
-#pragma unroll 2
-    for (int q = 0; q < 8; ++q) {  // 4 fp32 of K per chunk, two MFMAs of K=2
-      float4 a[4], b[2];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const float4*>(sa + lds_off(arow + i * 32, q));
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = *reinterpret_cast<const float4*>(sb + lds_off(brow + j * 32, q));
-      // lanes 0-31 supply K index 0 of each pair, lanes 32-63 index 1
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const float a0 = khalf ? a[i].y : a[i].x, b0 = khalf ? b[j].y : b[j].x;
-          const float a1 = khalf ? a[i].w : a[i].z, b1 = khalf ? b[j].w : b[j].z;
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[i][j], 0, 0, 0);
-        }
-    }
-    if (kt + 1 < nk) sstore(buf ^ 1);
-    __syncthreads();
-  }
-
-  ColIn<Acc32> ci;
-  const PosMap pos{p0, pt, npt, false};
-  load_col_inputs<Acc32, kMode>(ci, tid, lane, wp, pos, M, sa, ta);
-  epilogue<Acc32, kMode>(acc, smem, tid, lane, wv, wp, vt, v0, pos, M, V, partials, sa, ta, ci);
-}
-
 // Entry points: positions = hidden rows 0..M-1, or gathered through a row
 // list; greedy candidates only, drawn candidates as well, or the logits of
 // given tokens.  Separate symbols keep the row-list, drawing and target code
@@ -525,7 +418,6 @@ __device__ __forceinline__ void gemm_stats_f32_body(
                                    SampleArgs{}, ta);                                          \
   }
 FORK_GEMM_ENTRIES(bf16)
-FORK_GEMM_ENTRIES(f32)
 // Drawing over all rows with interleaved positions (M = 256 * npt).
 __global__ __launch_bounds__(kThreads) void gemm_stats_bf16_draw_ilv_kernel(FORK_GEMM_ARGS,
                                                                            SampleArgs sa) {
@@ -574,12 +466,12 @@ hipError_t launch_gemm_stats(const void* hidden, const void* W, bool bf16, int M
                              float4* partials, const int32_t* rowlist, int Mh,
                              const SampleArgs& sample, const TargetArgs& target,
                              hipStream_t stream) {
-  if (bf16) {
-    const TileChoice t = choose_tile(M, d, V);
-    if (t.narrow)
-      return launch_gemm_narrow(t.positions, t.nontemporal, hidden, W, M, d, V, partials, rowlist,
-                                Mh, sample, target, stream);
-  }
+  if (!bf16)
+    return launch_gemm_f32(hidden, W, M, d, V, partials, rowlist, Mh, sample, target, stream);
+  const TileChoice t = choose_tile(M, d, V);
+  if (t.narrow)
+    return launch_gemm_narrow(t.positions, t.nontemporal, hidden, W, M, d, V, partials, rowlist,
+                              Mh, sample, target, stream);
   const int nvt = num_vocab_tiles(V);
   const int npt = num_pos_tiles(M);
   const dim3 grid((unsigned)(nvt * npt)), block(kThreads);
@@ -589,32 +481,20 @@ hipError_t launch_gemm_stats(const void* hidden, const void* W, bool bf16, int M
   const bool tgt = target.token != nullptr;
 #define FORK_LAUNCH(K, ...) hipLaunchKernelGGL(K, grid, block, 0, stream, h, w, M, d, V, nvt, npt, \
                                                partials, ##__VA_ARGS__)
-  if (bf16 && rowlist && tgt)
+  if (rowlist && tgt)
     FORK_LAUNCH(gemm_stats_bf16_rows_target_kernel, rowlist, Mh, target);
-  else if (bf16 && tgt)
+  else if (tgt)
     FORK_LAUNCH(gemm_stats_bf16_target_kernel, target);
-  else if (!bf16 && rowlist && tgt)
-    FORK_LAUNCH(gemm_stats_f32_rows_target_kernel, rowlist, Mh, target);
-  else if (!bf16 && tgt)
-    FORK_LAUNCH(gemm_stats_f32_target_kernel, target);
-  else if (bf16 && rowlist && draw)
-    FORK_LAUNCH(gemm_stats_bf16_rows_draw_kernel, rowlist, Mh, sample);
-  else if (bf16 && draw && npt > 1 && M == npt * kTileP && (long long)M * d * 2 < (1LL << 31))
-    FORK_LAUNCH(gemm_stats_bf16_draw_ilv_kernel, sample);
-  else if (bf16 && rowlist)
-    FORK_LAUNCH(gemm_stats_bf16_rows_kernel, rowlist, Mh);
-  else if (bf16 && draw)
-    FORK_LAUNCH(gemm_stats_bf16_draw_kernel, sample);
-  else if (bf16)
-    FORK_LAUNCH(gemm_stats_bf16_kernel);
   else if (rowlist && draw)
-    FORK_LAUNCH(gemm_stats_f32_rows_draw_kernel, rowlist, Mh, sample);
+    FORK_LAUNCH(gemm_stats_bf16_rows_draw_kernel, rowlist, Mh, sample);
+  else if (draw && npt > 1 && M == npt * kTileP && (long long)M * d * 2 < (1LL << 31))
+    FORK_LAUNCH(gemm_stats_bf16_draw_ilv_kernel, sample);
   else if (rowlist)
-    FORK_LAUNCH(gemm_stats_f32_rows_kernel, rowlist, Mh);
+    FORK_LAUNCH(gemm_stats_bf16_rows_kernel, rowlist, Mh);
   else if (draw)
-    FORK_LAUNCH(gemm_stats_f32_draw_kernel, sample);
+    FORK_LAUNCH(gemm_stats_bf16_draw_kernel, sample);
   else
-    FORK_LAUNCH(gemm_stats_f32_kernel);
+    FORK_LAUNCH(gemm_stats_bf16_kernel);
 #undef FORK_LAUNCH
   return hipGetLastError();
 }

@@ -1,9 +1,9 @@
 // Device code shared by the LM-head kernels: operand swizzle, tile mapping,
 // accumulator layouts, the per-column statistics over the vocabulary and the
-// drawing of candidates.  Every kernel takes column_stats of the 128
+// drawing of candidates.  The bf16 kernels all take column_stats of the 128
 // vocabulary rows a wave holds and merge2 of a tile's two halves, in this
 // order, so the partials of a (position, tile) have the same bits whichever
-// kernel computed them.
+// kernel computed them; the fp32 kernels likewise over eight waves' 32 rows.
 #pragma once
 
 #include "fork_kernels.h"
@@ -16,7 +16,6 @@ namespace fork {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSlab = 128;                   // bytes of K per row per stage
@@ -98,18 +97,19 @@ __device__ __forceinline__ float gumbel_key(float z, float inv_tau, uint32_t w) 
   return fmaf(z, inv_tau, -__builtin_amdgcn_logf(e) * kLn2);
 }
 
-// Accumulator layouts.  In both, a lane's accumulators hold vocabulary values
-// (MFMA rows) of whole positions (MFMA columns), so the reduction over the
-// vocabulary is mostly in-lane.
+// Accumulator layout: a lane's accumulators hold vocabulary values (MFMA rows)
+// of whole positions (MFMA columns), so the reduction over the vocabulary is
+// mostly in-lane.
 //
-// AccN (bf16 path, v_mfma_f32_16x16x32_bf16): a wave's 128 x 16 N outputs are
-// 8 x N blocks of 16 x 16; element e of block (i, j) in lane l is row
-// 16 i + 4 (l / 16) + e, column 16 j + l % 16.  The four lanes l % 16 + 16 g
-// (g = 0..3) hold the 128 rows of a column, 32 each.
-template <int N>
+// AccN (16 x 16 MFMA blocks): a wave's 16 I x 16 N outputs are I x N blocks of
+// 16 x 16; element e of block (i, j) in lane l is row 16 i + 4 (l / 16) + e,
+// column 16 j + l % 16.  The four lanes l % 16 + 16 g (g = 0..3) hold the rows
+// of a column, 4 I each.
+template <int N, int I = 8>
 struct AccN {
-  typedef f32x4 Arr[8][N];
-  static constexpr int kNI = 8, kNJ = N, kNE = 4;
+  typedef f32x4 Arr[I][N];
+  static constexpr int kNI = I, kNJ = N, kNE = 4;
+  static constexpr int kRows = 16 * I;
   static constexpr int kLeaders = 16;  // lanes 0..15 hold one copy of each column
   __device__ static float get(const Arr& a, int i, int j, int e) { return a[i][j][e]; }
   __device__ static void set(Arr& a, int i, int j, int e, float v) { a[i][j][e] = v; }
@@ -123,25 +123,6 @@ struct AccN {
   }
 };
 typedef AccN<4> Acc16;
-
-// Acc32 (fp32 path, v_mfma_f32_32x32x2f32): 4 x 2 blocks of 32 x 32; element
-// e of block (i, j) in lane l is row 32 i + 8 (e / 4) + 4 (l / 32) + e % 4,
-// column 32 j + l % 32.  Lanes l and l ^ 32 hold the 128 rows of a column.
-struct Acc32 {
-  typedef f32x16 Arr[4][2];
-  static constexpr int kNI = 4, kNJ = 2, kNE = 16;
-  static constexpr int kLeaders = 32;
-  __device__ static float get(const Arr& a, int i, int j, int e) { return a[i][j][e]; }
-  __device__ static void set(Arr& a, int i, int j, int e, float v) { a[i][j][e] = v; }
-  __device__ static int row(int i, int e, int lane) {
-    return i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-  }
-  __device__ static int col(int j, int lane) { return j * 32 + (lane & 31); }
-  template <class F>
-  __device__ static void across(F&& f) {
-    f(32);
-  }
-};
 
 // What the epilogue produces besides the per-tile statistics.
 enum EpilogueMode { kGreedy = 0, kDrawn = 1, kTarget = 2 };
@@ -250,11 +231,11 @@ __device__ __forceinline__ void column_stats(typename Lay::Arr& acc, int j, int 
 }
 
 // The logit of row tk (a given token) in column j, if this lane holds it among
-// the 128 rows from vbase.
+// the wave's rows from vbase.
 template <class Lay>
 __device__ __forceinline__ bool column_target(const typename Lay::Arr& acc, int j, int lane,
                                               int vbase, int V, int tk, float& z) {
-  if (tk < vbase || tk >= vbase + 128 || tk >= V) return false;
+  if (tk < vbase || tk >= vbase + Lay::kRows || tk >= V) return false;
   bool hit = false;
 #pragma unroll
   for (int i = 0; i < Lay::kNI; ++i)
@@ -274,7 +255,7 @@ __device__ __forceinline__ float4 pick_drawn(float4 a, float4 b) {
   return make_float4(take_a ? a.x : b.x, take_a ? a.y : b.y, take_a ? a.z : b.z, 0.f);
 }
 
-// The maximiser of the Gumbel keys of column j over the 128 rows from vbase,
+// The maximiser of the Gumbel keys of column j over the wave's rows from vbase,
 // for the lanes whose column is drawn (srow >= 0): best key, its lowest row
 // and its logit, combined over the lanes holding the column.
 template <class Lay, bool kFull>

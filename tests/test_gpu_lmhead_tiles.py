@@ -1,5 +1,6 @@
 """The LM head's position tiles: launches of different sizes take tiles of 64,
-128 or 256 positions, and a row's statistics must not depend on which."""
+128 or 256 positions (fp32: 16, 32, 64 or 128), and a row's statistics must
+not depend on which."""
 import numpy as np
 import pytest
 import torch
@@ -12,10 +13,10 @@ pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
 
 
-def _inputs(M, d, V, seed):
+def _inputs(M, d, V, seed, dtype=torch.bfloat16):
     g = torch.Generator().manual_seed(seed)
-    W = (torch.randn(V, d, generator=g) / d ** 0.5).bfloat16()
-    h = (torch.randn(M, d, generator=g) * (0.5 + 1.5 * torch.rand(M, 1, generator=g))).bfloat16()
+    W = (torch.randn(V, d, generator=g) / d ** 0.5).to(dtype)
+    h = (torch.randn(M, d, generator=g) * (0.5 + 1.5 * torch.rand(M, 1, generator=g))).to(dtype)
     return h, W
 
 
@@ -40,13 +41,29 @@ def test_tile_edges_match_oracle(M, d, V):
     record(rep, "tiles")
 
 
+# fp32: edges of the 16-position columns, of a wave's 32 rows, of the tile, of
+# the K stages (32 elements) and of the 16-byte chunks
+@pytest.mark.parametrize("M", [1, 16, 17, 130])
+@pytest.mark.parametrize("d,V", [(4, 1), (32, 31), (36, 33), (132, 255), (256, 257), (68, 600)])
+def test_f32_tile_edges_match_oracle(M, d, V):
+    h, W = _inputs(M, d, V, M * 1000 + V, torch.float32)
+    g = _step(h, W)
+    ref = oracle.row_stats(host_bits(h), host_bits(W))
+    rep = Report()
+    compare_stats(g, ref, np.arange(M), host_bits(h), host_bits(W), d, rep)
+    record(rep, "tiles_f32")
+
+
 # V = 32000 (125 vocabulary tiles): 1024 rows take tiles of 256 positions, 160
-# rows tiles of 128, 40 rows tiles of 64; V = 2000 takes 64 throughout
-@pytest.mark.parametrize("V,sizes", [(32000, (40, 160, 1024)), (2000, (3, 70, 300))])
+# rows tiles of 128, 40 rows tiles of 64; V = 2000 takes 64 throughout; fp32
+# tiles of 16, 32, 64 and 128 in turn
+@pytest.mark.parametrize("V,sizes,dtype", [(32000, (40, 160, 1024), torch.bfloat16),
+                                           (2000, (3, 70, 300), torch.bfloat16),
+                                           (32000, (16, 48, 128, 256), torch.float32)])
 @pytest.mark.parametrize("temperature", [0.0, 0.8])
-def test_rows_do_not_depend_on_the_tile(V, sizes, temperature):
+def test_rows_do_not_depend_on_the_tile(V, sizes, dtype, temperature):
     d = 72
-    h, W = _inputs(max(sizes), d, V, V)
+    h, W = _inputs(max(sizes), d, V, V, dtype)
     outs = [_step(h[:n].contiguous(), W, temperature) for n in sizes]
     for n, g in zip(sizes[:-1], outs[:-1]):
         for k in ("conf", "entropy", "logp", "lse", "argmax"):
