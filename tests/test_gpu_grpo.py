@@ -200,6 +200,32 @@ def test_top_entropy_matches_oracle(R, Lg, k):
     assert np.all(got.sum(axis=1) == k)
 
 
+@pytest.mark.parametrize("Lg", [1, 63, 65, 256, 257, 512, 513, 2048, 2049, 5000])
+def test_top_entropy_values_and_sizes(Lg):
+    """Edges of the positions a lane and a wave hold; infinities, both zeros
+    (equal), negative values and NaN: a NaN is ordered before nothing and
+    nothing before it (selected whenever k > 0, not counted)."""
+    _need_gpu()
+    rng = np.random.default_rng(Lg)
+    ent = np.round(rng.normal(0, 1, (4, Lg)), 1).astype(np.float32)
+    ent[1] = np.where(rng.random(Lg) < 0.7, np.where(rng.random(Lg) < 0.5, 0.0, -0.0), ent[1])
+    ent[2][rng.random(Lg) < 0.2] = np.inf
+    ent[2][rng.random(Lg) < 0.2] = -np.inf
+    ent[3][rng.random(Lg) < 0.3] = np.nan
+    pos = np.arange(Lg)
+    for k in sorted({0, 1, Lg // 3, Lg - 1, Lg}):
+        want = np.zeros((4, Lg), np.uint8)
+        for r in range(4):
+            for p0 in range(0, Lg, 256):
+                p = pos[p0:p0 + 256, None]
+                h = ent[r][p]
+                ahead = (ent[r] > h) | ((ent[r] == h) & (pos < p))
+                want[r, p0:p0 + 256] = ahead.sum(axis=1) < k
+        sel = torch.full((4, Lg), 7, dtype=torch.uint8, device=DEV)
+        _binding.top_entropy(torch.as_tensor(ent, device=DEV), k, sel)
+        assert np.array_equal(sel.cpu().numpy(), want), k
+
+
 def test_forkgrpo_rollouts_and_objective():
     """A ForkGRPO batch end to end: 2 prompts x 16 rollouts decoded with
     Fork-dLLM (lambda = 0.8, candidates drawn at temperature 0.8), in
