@@ -2,7 +2,9 @@
 
 Argument marshalling only: shapes, dtypes, devices and contiguity are checked,
 then raw device pointers and the current HIP stream are handed to the library,
-where every step of the computation runs in HIP kernels.  There is no CPU or
+where every step of the computation runs in HIP kernels.  Plain calls (torch
+tensors, Python numbers) are checked and made natively (csrc/fastcall.cpp);
+anything else, and whatever fails a check there, goes through the checks here.  There is no CPU or
 PyTorch fallback: if the library is missing the first call raises.
 """
 from __future__ import annotations
@@ -94,12 +96,13 @@ class ForkError(RuntimeError):
 
 
 _lib = None
+_fast = None  # the native form of the plain calls (csrc/fastcall.cpp), if built
 
 
 def lib():
     """Load libforkstep.so (after torch, so that the HIP runtime torch already
     loaded is the one the library binds to)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -133,7 +136,30 @@ def lib():
         L.fork_top_entropy.restype = ctypes.c_int
         L.fork_top_entropy.argtypes = [_P, _I32, _I32, _I32, _P, _P]
         _lib = L
+        raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw_stream is not None and os.path.exists(os.path.join(_HERE, "_fastcall.so")):
+            from . import _fastcall
+            _fastcall.init(raw_stream, *(
+                ctypes.cast(f, _P).value for f in (
+                    L.fork_step_ex, L.fork_step_noalloc, L.fork_logprob, L.fork_grpo_objective,
+                    L.fork_select, L.fork_top_entropy)))
+            _fast = _fastcall
     return _lib
+
+
+def _plain(name, *args) -> bool:
+    """Make the call natively.  False if an argument is not of the plain form
+    or fails a check; the caller then checks and calls by itself."""
+    if _lib is None:
+        lib()
+    if _fast is None:
+        return False
+    rc = getattr(_fast, name)(*args)
+    if rc is None:
+        return False
+    if rc != FORK_OK:
+        _raise_on(rc)
+    return True
 
 
 def _check(t: torch.Tensor, name: str, dtype, numel: int, device) -> int:
@@ -183,6 +209,11 @@ def fork_step_ex(hidden: torch.Tensor, W_head: torch.Tensor, tokens: torch.Tenso
     """fork_step_ex of the C ABI; optional outputs may be None.  ``events``
     is an optional pair of raw hipEvent_t handles (ints) recorded around the
     LM-head kernel."""
+    if _plain("step", False, hidden, W_head, tokens, mask, block_start, block_len, tau, out_conf,
+              out_entropy, out_logp, out_fallback, B, L, out_lse, out_argmax, out_ncommit,
+              out_commit_pos, rule, workspace, stream, events, fallback_uniform, rows_mode,
+              temperature, seed, counter):
+        return
     a = _step_args(hidden, W_head, tokens, mask, block_start, block_len, tau, out_conf,
                    out_entropy, out_logp, out_fallback, B, L, out_lse, out_argmax,
                    out_ncommit, out_commit_pos, rule, workspace, stream, events,
@@ -200,6 +231,11 @@ def fork_step_noalloc(hidden: torch.Tensor, W_head: torch.Tensor, tokens: torch.
                       temperature: float = 0.0, seed: int = 0, counter: int = 0) -> None:
     """fork_step_noalloc of the C ABI: fork_step_ex on the library's static
     device scratch (allocates nothing)."""
+    if _plain("step", True, hidden, W_head, tokens, mask, block_start, block_len, tau, out_conf,
+              out_entropy, out_logp, out_fallback, B, L, out_lse, out_argmax, out_ncommit,
+              out_commit_pos, rule, None, stream, events, fallback_uniform, rows_mode,
+              temperature, seed, counter):
+        return
     a = _step_args(hidden, W_head, tokens, mask, block_start, block_len, tau, out_conf,
                    out_entropy, out_logp, out_fallback, B, L, out_lse, out_argmax,
                    out_ncommit, out_commit_pos, rule, None, stream, events,
@@ -271,6 +307,9 @@ def logprob(hidden: torch.Tensor, W_head: torch.Tensor, tokens: torch.Tensor,
             out_entropy=None, out_lse=None, workspace=None, stream=None, events=None) -> None:
     """fork_logprob of the C ABI: log q(tokens[e]) at hidden row rows[e]
     (row e without ``rows``) under W_head."""
+    if _plain("logprob", hidden, W_head, tokens, out_logp, rows, out_q, out_entropy, out_lse,
+              workspace, stream, events):
+        return
     if hidden.dim() != 2 or W_head.dim() != 2:
         raise ValueError("hidden and W_head must be 2-D")
     device = hidden.device
@@ -310,6 +349,9 @@ def grpo_objective(rewards: torch.Tensor, offsets: torch.Tensor, lp_new: torch.T
                    out_ratio=None, out_term=None, out_rollout_obj=None, stream=None) -> None:
     """fork_grpo_objective of the C ABI (rewards [n_groups*G], offsets
     [n_groups*G + 1], lp_new / lp_old [n])."""
+    if _plain("grpo", rewards, offsets, lp_new, lp_old, G, eps, out_group_obj, out_skipped, out_J,
+              out_adv, out_ratio, out_term, out_rollout_obj, stream):
+        return
     device = rewards.device
     if device.type != "cuda":
         raise ValueError("fork_grpo_objective runs on the GPU")
@@ -338,6 +380,8 @@ def grpo_objective(rewards: torch.Tensor, offsets: torch.Tensor, lp_new: torch.T
 
 def top_entropy(entropy: torch.Tensor, k: int, out_sel: torch.Tensor, stream=None) -> None:
     """fork_top_entropy of the C ABI on an [R, Lg] float32 tensor."""
+    if _plain("top_entropy", entropy, k, out_sel, stream):
+        return
     if entropy.dim() != 2:
         raise ValueError("entropy must be [R, Lg]")
     device = entropy.device
@@ -357,6 +401,9 @@ def select(conf: torch.Tensor, argmax: torch.Tensor, tokens: torch.Tensor, mask:
     """fork_select of the C ABI: the unmasking rule alone, in place.  With
     FORK_LAYOUT_POSITION_MAJOR the per-position tensors hold position k of
     sequence b at k*B + b."""
+    if _plain("select", conf, argmax, tokens, mask, block_start, block_len, tau, out_fallback, B,
+              L, rule, entropy, uniform, out_ncommit, out_commit_pos, stream, layout):
+        return
     device = conf.device
     if device.type != "cuda":
         raise ValueError("fork_select runs on the GPU")

@@ -2,7 +2,8 @@
 
 ``python -m paper_2609_39859_amd.build`` compiles the library's HIP sources
 under csrc/ with hipcc into libforkstep.so next to this file, and the
-benchmark's peak probes (csrc/peak_probe.hip) into libforkprobe.so.  The compile
+benchmark's peak probes (csrc/peak_probe.hip) into libforkprobe.so, and with
+g++ the Python binding's native calls into _fastcall.so.  The hipcc compile
 disables packed-fp32 instruction selection (the -packed-fp32-ops target
 feature); hipcc's host pass warns that it does not know the feature, which is
 harmless.
@@ -42,10 +43,43 @@ def build(verbose: bool = False) -> str:
     """Compile and link libforkstep.so and libforkprobe.so, then the plain-C
     example that drives one step through the C ABI; returns the path of
     libforkstep.so."""
+    fast = build_fastcall(verbose)
     _build_lib(PROBE_LIB, PROBE_SOURCES, verbose)
     lib = _build_lib(LIB, SOURCES, verbose)
     build_c_example(verbose)
+    _finish(fast)
     return lib
+
+
+FASTCALL = os.path.join(HERE, "_fastcall.so")
+
+
+def build_fastcall(verbose: bool = False):
+    """Start the host compile of _fastcall.so (csrc/fastcall.cpp: the Python
+    binding's plain calls, against torch's headers); _finish() ends it."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    libdir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = FASTCALL + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-I", INCLUDE,
+           "-I", sysconfig.get_paths()["include"],
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    for inc in include_paths():
+        cmd += ["-isystem", inc]
+    cmd += [os.path.join(CSRC, "fastcall.cpp"), "-L", libdir, "-ltorch_python", "-ltorch_cpu",
+            "-lc10", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    return subprocess.Popen(cmd), tmp
+
+
+def _finish(job) -> None:
+    p, tmp = job
+    if p.wait():
+        raise RuntimeError("g++ failed for fastcall.cpp")
+    os.replace(tmp, FASTCALL)
 
 
 C_EXAMPLE_SRC = os.path.join(ROOT, "tests", "native", "abi_c_step.c")
