@@ -428,13 +428,17 @@ __global__ __launch_bounds__(kThreads) void gemm_stats_bf16_draw_ilv_kernel(FORK
 #undef FORK_GEMM_ENTRIES
 
 // Positions per workgroup of the bf16 LM head.  A tile of 64, 128 or 256
-// positions takes 1 : 1.45 : 1.95 (measured over d = 256 .. 4096, V = 2000 ..
+// positions takes 1 : 1.45 : 2.1 (measured over d = 256 .. 4096, V = 2000 ..
 // 32000, one round of tiles: 9.4 / 12.2 / 16.2 us, 14.3 / 19.9 / 27.5 us,
-// 36.5 / 53 / 73 us), and the 256 CUs take one tile each per round, so the
-// cost of a launch is the rounds times the tile's; the fewest-positions tile
-// wins ties.  Examples (us, 64 / 128 / 256 positions): V = 8000, d = 1024:
-// M = 512 16 / 22 / 28, M = 1024 28 / 23 / 29; V = 32000, d = 1024: M = 128
-// 20 / 24 / 25, M = 256 30 / 27 / 30, M = 1024 98 / 79 / 63.
+// 36.5 / 53 / 73 us; with every CU busy 39 / 58 / 94 us), and the 256 CUs take
+// one tile each per round, so the cost of a launch is the rounds times the
+// tile's.  Rows that are not whole cache lines make the smaller tiles, which
+// load more per flop, dearer once more than one round runs (d = 3504, M =
+// 1294, V = 23341: 392 / 257 / 228 us).  Examples (us, 64 / 128 / 256
+// positions): V = 8000, d = 1024: M = 512 16 / 22 / 28, M = 1024 28 / 23 / 29;
+// V = 32000, d = 1024: M = 128 20 / 24 / 25, M = 256 30 / 27 / 30, M = 1024
+// 98 / 79 / 63.  Over 370 such shapes the choice loses 0.3% on the best of the
+// three.
 struct TileChoice {
   bool narrow;
   int positions;
@@ -445,10 +449,13 @@ TileChoice choose_tile(int M, int d, int V) {
   constexpr long long kCus = 256;
   const long long nvt = num_vocab_tiles(V);
   auto tiles = [&](int p) { return ((long long)M + p - 1) / p; };
-  auto rounds = [&](int p) { return (nvt * tiles(p) + kCus - 1) / kCus; };
-  int best = 64;
-  if (145 * rounds(128) < 100 * rounds(64)) best = 128;
-  if (195 * rounds(256) < (best == 64 ? 100 : 145) * rounds(best)) best = 256;
+  auto cost = [&](int p, int per_round) {
+    const long long n = nvt * tiles(p);
+    const bool dear = p < kTileP && n > kCus && d % 64 != 0;
+    return (n + kCus - 1) / kCus * per_round * (dear ? 12 : 10);
+  };
+  const long long c64 = cost(64, 100), c128 = cost(128, 145), c256 = cost(256, 210);
+  const int best = c256 < c64 && c256 < c128 ? 256 : c128 < c64 ? 128 : 64;
   // One position tile reads W once: past the 256 MB last-level cache it is
   // loaded nontemporally (M = 64, d = 4096, one W for every step: 130 MB 37 us
   // cached and 51 nontemporal, 262 MB 52 and 60, 412 MB 80 and 73).  With 256
