@@ -61,7 +61,7 @@ hipError_t launch_gemm_narrow(int positions, bool nontemporal, const void* hidde
                               int Mh, const SampleArgs& sample, const TargetArgs& target,
                               hipStream_t stream);
 
-// The same for fp32 inputs.
+// launch_gemm_stats for fp32 inputs.
 hipError_t launch_gemm_f32(const void* hidden, const void* W, int M, int d, int V,
                            float4* partials, const int32_t* rowlist, int Mh,
                            const SampleArgs& sample, const TargetArgs& target,

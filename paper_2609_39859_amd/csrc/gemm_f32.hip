@@ -46,7 +46,7 @@ __device__ __forceinline__ void gemm_f32_body(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   int vt, pt;
-  map_tile(blockIdx.x, nvt, npt, vt, pt);
+  map_tile(blockIdx.x, nvt * npt, nvt, npt, vt, pt);
   const int v0 = vt * kTileV;
   const int p0 = (pt0 + pt) * kTP;
 

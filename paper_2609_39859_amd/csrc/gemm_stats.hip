@@ -51,7 +51,7 @@
 // exponential draw built from Philox4x32-10 (Salmon et al., SC'11) at
 // counter (v / 4, row, step counter, 0): one generator call serves the four
 // consecutive vocabulary entries a lane holds in one accumulator group.
-#include "lmhead_device.h"
+#include "gemm_narrow_body.h"
 
 namespace fork {
 namespace {
@@ -128,13 +128,27 @@ __device__ __forceinline__ void epilogue(typename Lay::Arr& acc, unsigned char* 
                                      sa, ta, ci);
 }
 
-template <int kMode, bool kIlv = false>
+template <int kMode, bool kIlv, bool kTail>
 __device__ __forceinline__ void gemm_stats_bf16_body(
     const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ W, int M, int d,
-    int V, int nvt, int npt, float4* __restrict__ partials, const int32_t* __restrict__ rowlist,
-    int Mh, const SampleArgs& sa, const TargetArgs& ta) {
+    int V, int nvt, int npt, int nbig, float4* __restrict__ partials,
+    const int32_t* __restrict__ rowlist, int Mh, const SampleArgs& sa, const TargetArgs& ta) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the name
   // W ring: slots 0..2; hidden ring: slots 3..4
   __shared__ __attribute__((aligned(1024))) unsigned char smem[5 * kOperandBytes];
+
+  // kTail: workgroups past the first nbig take a quarter of a tile each, 64
+  // positions of the tiles from nbig on (see tail_tiles).
+  if (kTail && (int)blockIdx.x >= nbig) {
+    const int quarter = xcd_order(blockIdx.x - nbig, gridDim.x - nbig);
+    int vt, pt;
+    tile_of(nbig + (quarter >> 2), nvt, npt, vt, pt);
+    const int p0 = pt * kTileP + (quarter & 3) * 64;
+    if (p0 < M)
+      gemm_narrow_body<1, false, kMode>(smem, hidden, W, M, d, V, vt, p0, partials, rowlist, Mh,
+                                        sa, ta);
+    return;
+  }
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -143,7 +157,7 @@ __device__ __forceinline__ void gemm_stats_bf16_body(
   const int wp = wave >> 1;  // position quarter: cols wp*64 .. +64
 
   int vt, pt;
-  map_tile(blockIdx.x, nvt, npt, vt, pt);
+  map_tile(blockIdx.x, nbig, nvt, npt, vt, pt);
   const int v0 = vt * kTileV;
   const int p0 = pt * kTileP;
   const PosMap pos{p0, pt, npt, kIlv};
@@ -378,6 +392,7 @@ __device__ __forceinline__ void gemm_stats_bf16_body(
   barrier_nofence();
 
   epilogue<Acc16, kMode>(acc, smem, tid, lane, wv, wp, vt, v0, pos, M, V, partials, sa, ta, ci);
+#endif
 }
 
 // Entry points: positions = hidden rows 0..M-1, or gathered through a row
@@ -386,42 +401,48 @@ __device__ __forceinline__ void gemm_stats_bf16_body(
 // out of the dense greedy kernel and the variants apart in kernel traces.
 #define FORK_GEMM_ARGS                                                                         \
   const unsigned char *__restrict__ hidden, const unsigned char *__restrict__ W, int M, int d, \
-      int V, int nvt, int npt, float4 *__restrict__ partials
+      int V, int nvt, int npt, int nbig, float4 *__restrict__ partials
 #define FORK_GEMM_ENTRIES(T)                                                                   \
+  template <bool kTail>                                                                        \
   __global__ __launch_bounds__(kThreads) void gemm_stats_##T##_kernel(FORK_GEMM_ARGS) {       \
-    gemm_stats_##T##_body<kGreedy>(hidden, W, M, d, V, nvt, npt, partials, nullptr, M,         \
+    gemm_stats_##T##_body<kGreedy, false, kTail>(hidden, W, M, d, V, nvt, npt, nbig, partials, nullptr, M,         \
                                    SampleArgs{}, TargetArgs{});                                \
   }                                                                                            \
+  template <bool kTail>                                                                        \
   __global__ __launch_bounds__(kThreads) void gemm_stats_##T##_rows_kernel(                   \
       FORK_GEMM_ARGS, const int32_t* __restrict__ rowlist, int Mh) {                           \
-    gemm_stats_##T##_body<kGreedy>(hidden, W, M, d, V, nvt, npt, partials, rowlist, Mh,        \
+    gemm_stats_##T##_body<kGreedy, false, kTail>(hidden, W, M, d, V, nvt, npt, nbig, partials, rowlist, Mh,        \
                                    SampleArgs{}, TargetArgs{});                                \
   }                                                                                            \
+  template <bool kTail>                                                                        \
   __global__ __launch_bounds__(kThreads) void gemm_stats_##T##_draw_kernel(FORK_GEMM_ARGS,    \
                                                                           SampleArgs sa) {     \
-    gemm_stats_##T##_body<kDrawn>(hidden, W, M, d, V, nvt, npt, partials, nullptr, M, sa,      \
+    gemm_stats_##T##_body<kDrawn, false, kTail>(hidden, W, M, d, V, nvt, npt, nbig, partials, nullptr, M, sa,      \
                                   TargetArgs{});                                               \
   }                                                                                            \
+  template <bool kTail>                                                                        \
   __global__ __launch_bounds__(kThreads) void gemm_stats_##T##_rows_draw_kernel(              \
       FORK_GEMM_ARGS, const int32_t* __restrict__ rowlist, int Mh, SampleArgs sa) {            \
-    gemm_stats_##T##_body<kDrawn>(hidden, W, M, d, V, nvt, npt, partials, rowlist, Mh, sa,     \
+    gemm_stats_##T##_body<kDrawn, false, kTail>(hidden, W, M, d, V, nvt, npt, nbig, partials, rowlist, Mh, sa,     \
                                   TargetArgs{});                                               \
   }                                                                                            \
+  template <bool kTail>                                                                        \
   __global__ __launch_bounds__(kThreads) void gemm_stats_##T##_target_kernel(FORK_GEMM_ARGS,  \
                                                                             TargetArgs ta) {   \
-    gemm_stats_##T##_body<kTarget>(hidden, W, M, d, V, nvt, npt, partials, nullptr, M,         \
+    gemm_stats_##T##_body<kTarget, false, kTail>(hidden, W, M, d, V, nvt, npt, nbig, partials, nullptr, M,         \
                                    SampleArgs{}, ta);                                          \
   }                                                                                            \
+  template <bool kTail>                                                                        \
   __global__ __launch_bounds__(kThreads) void gemm_stats_##T##_rows_target_kernel(            \
       FORK_GEMM_ARGS, const int32_t* __restrict__ rowlist, int Mh, TargetArgs ta) {            \
-    gemm_stats_##T##_body<kTarget>(hidden, W, M, d, V, nvt, npt, partials, rowlist, Mh,        \
+    gemm_stats_##T##_body<kTarget, false, kTail>(hidden, W, M, d, V, nvt, npt, nbig, partials, rowlist, Mh,        \
                                    SampleArgs{}, ta);                                          \
   }
 FORK_GEMM_ENTRIES(bf16)
 // Drawing over all rows with interleaved positions (M = 256 * npt).
 __global__ __launch_bounds__(kThreads) void gemm_stats_bf16_draw_ilv_kernel(FORK_GEMM_ARGS,
                                                                            SampleArgs sa) {
-  gemm_stats_bf16_body<kDrawn, true>(hidden, W, M, d, V, nvt, npt, partials, nullptr, M, sa,
+  gemm_stats_bf16_body<kDrawn, true, false>(hidden, W, M, d, V, nvt, npt, nbig, partials, nullptr, M, sa,
                                      TargetArgs{});
 }
 #undef FORK_GEMM_ARGS
@@ -445,8 +466,21 @@ struct TileChoice {
   bool nontemporal;
 };
 
+constexpr long long kCus = 256;
+
+// Tiles of 256 positions left in a last round that takes at most a quarter of
+// the CUs after a few whole rounds: such tiles run as four workgroups of 64
+// positions each, at the end of the same launch, so that they start on the
+// CUs that finish first (M = 903, d = 1544, V = 50257, 788 tiles: step 192 ->
+// 180 us; in a launch of their own 190).  Kernels with this path run their
+// 256-position tiles 4% slower than those without, so it pays for at most six
+// rounds.  0 if there are none.
+int tail_tiles(long long n) {
+  const long long rem = n % kCus, full = n / kCus;
+  return full >= 1 && full <= 6 && rem > 0 && rem <= kCus / 4 ? (int)rem : 0;
+}
+
 TileChoice choose_tile(int M, int d, int V) {
-  constexpr long long kCus = 256;
   const long long nvt = num_vocab_tiles(V);
   auto tiles = [&](int p) { return ((long long)M + p - 1) / p; };
   auto cost = [&](int p, int per_round) {
@@ -454,7 +488,8 @@ TileChoice choose_tile(int M, int d, int V) {
     const bool dear = p < kTileP && n > kCus && d % 64 != 0;
     return (n + kCus - 1) / kCus * per_round * (dear ? 12 : 10);
   };
-  const long long c64 = cost(64, 100), c128 = cost(128, 145), c256 = cost(256, 210);
+  const long long c64 = cost(64, 100), c128 = cost(128, 145);
+  const long long c256 = cost(256, 210) - (tail_tiles(nvt * tiles(256)) ? 1050 : 0);
   const int best = c256 < c64 && c256 < c128 ? 256 : c128 < c64 ? 128 : 64;
   // One position tile reads W once: past the 256 MB last-level cache it is
   // loaded nontemporally (M = 64, d = 4096, one W for every step: 130 MB 37 us
@@ -481,21 +516,32 @@ hipError_t launch_gemm_stats(const void* hidden, const void* W, bool bf16, int M
                               Mh, sample, target, stream);
   const int nvt = num_vocab_tiles(V);
   const int npt = num_pos_tiles(M);
-  const dim3 grid((unsigned)(nvt * npt)), block(kThreads);
-  const auto* h = static_cast<const unsigned char*>(hidden);
-  const auto* w = static_cast<const unsigned char*>(W);
   const bool draw = sample.row != nullptr;
   const bool tgt = target.token != nullptr;
-#define FORK_LAUNCH(K, ...) hipLaunchKernelGGL(K, grid, block, 0, stream, h, w, M, d, V, nvt, npt, \
-                                               partials, ##__VA_ARGS__)
+  const bool ilv = draw && !rowlist && npt > 1 && M == npt * kTileP &&
+                   (long long)M * d * 2 < (1LL << 31);
+  const int tail = ilv ? 0 : tail_tiles((long long)nvt * npt);
+  const int nbig = nvt * npt - tail;
+  const dim3 grid((unsigned)(nbig + 4 * tail)), block(kThreads);
+  const auto* h = static_cast<const unsigned char*>(hidden);
+  const auto* w = static_cast<const unsigned char*>(W);
+#define FORK_LAUNCH1(K, ...) hipLaunchKernelGGL((K), grid, block, 0, stream, h, w, M, d, V, nvt, npt, \
+                                                nbig, partials, ##__VA_ARGS__)
+#define FORK_LAUNCH(K, ...)                     \
+  do {                                          \
+    if (tail)                                   \
+      FORK_LAUNCH1(K<true>, ##__VA_ARGS__);     \
+    else                                        \
+      FORK_LAUNCH1(K<false>, ##__VA_ARGS__);    \
+  } while (0)
   if (rowlist && tgt)
     FORK_LAUNCH(gemm_stats_bf16_rows_target_kernel, rowlist, Mh, target);
   else if (tgt)
     FORK_LAUNCH(gemm_stats_bf16_target_kernel, target);
   else if (rowlist && draw)
     FORK_LAUNCH(gemm_stats_bf16_rows_draw_kernel, rowlist, Mh, sample);
-  else if (draw && npt > 1 && M == npt * kTileP && (long long)M * d * 2 < (1LL << 31))
-    FORK_LAUNCH(gemm_stats_bf16_draw_ilv_kernel, sample);
+  else if (ilv)
+    FORK_LAUNCH1(gemm_stats_bf16_draw_ilv_kernel, sample);
   else if (rowlist)
     FORK_LAUNCH(gemm_stats_bf16_rows_kernel, rowlist, Mh);
   else if (draw)
@@ -503,6 +549,7 @@ hipError_t launch_gemm_stats(const void* hidden, const void* W, bool bf16, int M
   else
     FORK_LAUNCH(gemm_stats_bf16_kernel);
 #undef FORK_LAUNCH
+#undef FORK_LAUNCH1
   return hipGetLastError();
 }
 

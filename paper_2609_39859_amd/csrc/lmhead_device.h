@@ -34,13 +34,15 @@ __device__ __forceinline__ int lds_off(int row, int chunk) {
   return row * kSlab + ((chunk ^ swz(row)) << 4);
 }
 
-// Maps the hardware workgroup id to (vocabulary tile, position tile).
-__device__ __forceinline__ void map_tile(int bid, int nvt, int npt, int& vt, int& pt) {
-  const int n = nvt * npt;
-  // Workgroups are dealt to the XCDs round-robin: XCD x gets x, x+8, ...
+// Workgroup id `bid` of `n` in the order of its XCD: workgroups are dealt to the
+// XCDs round-robin (XCD x gets x, x + 8, ...), each takes a contiguous range.
+__device__ __forceinline__ int xcd_order(int bid, int n) {
   const int x = bid % kXcds, i = bid / kXcds;
-  const int base = n / kXcds, rem = n % kXcds;
-  const int logical = x * base + min(x, rem) + i;
+  return x * (n / kXcds) + min(x, n % kXcds) + i;
+}
+
+// (vocabulary tile, position tile) of a place in the launch order.
+__device__ __forceinline__ void tile_of(int logical, int nvt, int npt, int& vt, int& pt) {
   const int per_group = kGroupV * npt;
   const int group = logical / per_group;
   const int in = logical - group * per_group;
@@ -48,6 +50,11 @@ __device__ __forceinline__ void map_tile(int bid, int nvt, int npt, int& vt, int
   const int gvn = min(kGroupV, nvt - gv0);
   pt = in / gvn;
   vt = gv0 + (in - pt * gvn);
+}
+
+// Maps the hardware workgroup id (of the first n) to its tile.
+__device__ __forceinline__ void map_tile(int bid, int n, int nvt, int npt, int& vt, int& pt) {
+  tile_of(xcd_order(bid, n), nvt, npt, vt, pt);
 }
 
 // Merge of two partials (either may be empty, s == 0).

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import oracle
+from paper_2609_39859_amd import _binding
 from harness import Report, compare_stats, gpu_step, host_bits, record
 
 pytestmark = pytest.mark.gpu
@@ -69,3 +70,25 @@ def test_rows_do_not_depend_on_the_tile(V, sizes, dtype, temperature):
         for k in ("conf", "entropy", "logp", "lse", "argmax"):
             a, b = getattr(g, k), getattr(outs[-1], k)[:n]
             assert np.array_equal(a.view(np.int32), b.view(np.int32)), (k, n)
+
+
+# 788, 260 and 288 tiles of 256 positions: the 20, 4 and 32 past the whole
+# rounds of 256 run as quarters, the last positions and words among them
+@pytest.mark.parametrize("M,d,V", [(903, 72, 50257), (1030, 40, 13300), (2100, 64, 8000)])
+def test_quartered_tail_matches_whole_tiles(M, d, V):
+    h, W = _inputs(M, d, V, M)
+    full = {t: _step(h, W, t) for t in (0.0, 0.8)}
+    for rows, temperature in ((slice(0, 700), 0.0), (slice(0, 700), 0.8),
+                              (slice(M - 60, M), 0.0)):  # draws depend on the row's index
+        g = _step(h[rows].contiguous(), W, temperature)
+        for k in ("conf", "entropy", "logp", "lse", "argmax"):
+            a, b = getattr(g, k), getattr(full[temperature], k)[rows]
+            assert np.array_equal(a.view(np.int32), b.view(np.int32)), (k, rows, temperature)
+    hd, Wd = h.to(DEV), W.to(DEV)
+    toks = torch.arange(M, dtype=torch.int32, device=DEV) * 7919 % V
+    lp = torch.zeros(M, device=DEV)
+    _binding.logprob(hd, Wd, toks, lp)
+    for rows in (slice(0, 700), slice(M - 60, M)):
+        part = torch.zeros_like(lp[rows])
+        _binding.logprob(hd[rows].contiguous(), Wd, toks[rows].contiguous(), part)
+        assert torch.equal(part.view(torch.int32), lp[rows].view(torch.int32)), rows
