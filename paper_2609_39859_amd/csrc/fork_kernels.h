@@ -94,13 +94,16 @@ hipError_t launch_active_rows(int B, int L, int block_len, const uint8_t* mask,
 // Unmasking rule per sequence, in place.  ncommit / commit_pos may be null;
 // entropy is read by the highest-entropy rule, uniform by the random rule.
 // Row-major state (element k of sequence b at b * L + k): batches of at
-// least kLaneSelectMinB sequences with blocks of at most kLaneSelectMaxBL
-// positions run one lane per sequence, others one wave per sequence.
+// least kGroupSelectMinB sequences with blocks of at most kGroupSelectMaxBL
+// positions run a group of lanes per sequence (eight from kGroupEightMinB
+// sequences on, four below), others one wave per sequence (as fast up to 4096
+// sequences: 6.3 us, the launch's latency).
 // Position-major state (at k * B + b): one lane per four sequences from
 // kPmWideMinB sequences on (B a multiple of 4, the arrays 16-byte aligned),
 // one lane per sequence otherwise.  All give the same results.
-constexpr int kLaneSelectMinB = 4096;
-constexpr int kLaneSelectMaxBL = 64;
+constexpr int kGroupSelectMinB = 4096;
+constexpr int kGroupSelectMaxBL = 64;
+constexpr int kGroupEightMinB = 1 << 18;
 constexpr int kPmWideMinB = 1 << 18;
 hipError_t launch_select(int B, int L, int block_len, float tau, int rule,
                          const float* conf, const float* entropy, const float* uniform,

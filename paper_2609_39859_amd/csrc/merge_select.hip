@@ -505,103 +505,197 @@ __device__ void lane_rule(int b, int s, int L, int BL, float tau, int rule,
   if (ncommit) ncommit[b] = written;
 }
 
-// The same rule with one lane per sequence, for large batches of short
-// blocks: each lane walks its block position by position, so a wave keeps
-// the loads of 64 sequences in flight instead of one (the wave-per-sequence
-// kernel is latency-bound once B reaches thousands).  Decisions are those of
-// select_kernel: binary32 threshold test, lowest position on ties.
-__global__ __launch_bounds__(256) void select_lanes_kernel(
+// Value of the lane d apart within a group of lanes, d = 1, 2, or (for values
+// equal over each four lanes) 4.
+template <int kD>
+__device__ __forceinline__ int group_xor(int v) {
+  constexpr int kCtrl = kD == 1 ? 0xB1 : kD == 2 ? 0x4E : 0x141;  // quad_perm, row_half_mirror
+  return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xf, 0xf, true);
+}
+
+// Lowest set bit and bit count of a block's mask.
+__device__ __forceinline__ int low_bit(uint32_t m) { return __ffs((int)m) - 1; }
+__device__ __forceinline__ int low_bit(uint64_t m) { return __ffsll((long long)m) - 1; }
+__device__ __forceinline__ int bit_count(uint32_t m) { return (int)__popc(m); }
+__device__ __forceinline__ int bit_count(uint64_t m) { return (int)__popcll(m); }
+
+// The same rule with G lanes per sequence, for large batches of blocks of at
+// most 32 Q positions (Q = 1, 2), 32 Q / G positions per lane: a wave's loads
+// cover the whole cache lines of 64 / G sequences' blocks, where one lane per
+// sequence (the kernel before) touched 64 lines with each load.  What remains
+// are the commits: a candidate read, a token and a mask byte written, each in
+// a line of its own.
+// One lane per sequence -> G = 4 / G = 8, us, the launch's 6 us of latency
+// included: 4096 sequences x blocks of 32 7.2 -> 6.4 / 6.2, 2^17 14.8 -> 15.0 /
+// 15.6, 2^20 116 -> 97 / 89; 2^17 with the highest-entropy rule or rows off the
+// 16-byte grid 40 -> 20 / 18; 2^17 x blocks of 64 127 -> 24 / 23.  Hence four
+// lanes below kGroupEightMinB sequences, eight above and for blocks over 32.
+// Lane t of a group holds the positions 4 G q + 4 t + {0..3} of the block if its
+// 32 Q entries lie in the row and are aligned for that, else 4 G q + t + {0, G,
+// 2 G, 3 G}.
+template <int Q, int G>
+__global__ __launch_bounds__(256) void select_group_kernel(
     int B, int L, int BL, float tau, int rule, const float* __restrict__ conf,
     const float* __restrict__ entropy, const float* __restrict__ uniform,
     const int32_t* __restrict__ argmax, int32_t* __restrict__ tokens,
     uint8_t* __restrict__ mask, int32_t* __restrict__ block_start,
     int32_t* __restrict__ fallback, int32_t* __restrict__ ncommit,
     int32_t* __restrict__ commit_pos) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
+  typedef typename std::conditional<Q == 1, uint32_t, uint64_t>::type Bits;
+  constexpr int N = 8 * Q / G;  // quads of positions per lane
+  const int b = blockIdx.x * (256 / G) + threadIdx.x / G;
+  const int t = threadIdx.x & (G - 1);
   if (b >= B) return;
   const size_t base = (size_t)b * L;
   int32_t* my_commits = commit_pos ? commit_pos + (size_t)b * BL : nullptr;
-  int s = block_start[b];
-  if (s < 0 || s > L) {
-    fallback[b] = -2;
-    if (ncommit) ncommit[b] = 0;
-    if (my_commits)
-      for (int i = 0; i < BL; ++i) my_commits[i] = -1;
+  const int s = block_start[b];
+  const float* key = rule == kMaxEnt ? entropy : conf;
+  uint32_t mw[Q] = {}, pw[Q] = {};
+  float kv[4 * N];
+  bool wide = false;
+  // the lane's j-th position of its quad q within the block; word 4 G q / 32
+  auto pos = [&](int q, int j) { return 4 * G * q + (wide ? 4 * t + j : t + G * j); };
+  if (s >= 0 && s < L) {
+    const int cnt = min(BL, L - s);
+    const uint8_t* mb = mask + base + s;
+    const float *cb = conf + base + s, *kb = key + base + s;
+    wide = s + 32 * Q <= L &&
+           ((reinterpret_cast<uintptr_t>(cb) | reinterpret_cast<uintptr_t>(kb)) & 15) == 0 &&
+           (reinterpret_cast<uintptr_t>(mb) & 3) == 0;
+    uint32_t m4[N] = {};  // mask bytes of the lane's positions
+    float c[4 * N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c[4 * q + j] = kv[4 * q + j] = 0.f;
+      if (wide) {
+        const int p = 4 * G * q + 4 * t;
+        if (p < cnt) {
+          m4[q] = *reinterpret_cast<const uint32_t*>(mb + p);
+          const float4 v = *reinterpret_cast<const float4*>(cb + p);
+          c[4 * q] = v.x, c[4 * q + 1] = v.y, c[4 * q + 2] = v.z, c[4 * q + 3] = v.w;
+          if (rule == kMaxEnt) {
+            const float4 u = *reinterpret_cast<const float4*>(kb + p);
+            kv[4 * q] = u.x, kv[4 * q + 1] = u.y, kv[4 * q + 2] = u.z, kv[4 * q + 3] = u.w;
+          }
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int p = 4 * G * q + t + G * j;
+          if (p < cnt) {
+            m4[q] |= (uint32_t)mb[p] << (8 * j);
+            c[4 * q + j] = cb[p];
+            if (rule == kMaxEnt) kv[4 * q + j] = kb[p];
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int p = pos(q, j);
+        const bool m = p < cnt && ((m4[q] >> (8 * j)) & 0xffu) != 0;
+        mw[G * q / 8] |= (uint32_t)m << (p & 31);
+        pw[G * q / 8] |= (uint32_t)(m && c[4 * q + j] > tau) << (p & 31);
+        if (rule != kMaxEnt) kv[4 * q + j] = c[4 * q + j];
+      }
+  }
+  // the block's masks: the same for its eight lanes
+  Bits mbits = 0, pbits = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    mw[q] |= (uint32_t)group_xor<1>((int)mw[q]);
+    pw[q] |= (uint32_t)group_xor<1>((int)pw[q]);
+    mw[q] |= (uint32_t)group_xor<2>((int)mw[q]);
+    pw[q] |= (uint32_t)group_xor<2>((int)pw[q]);
+    if (G == 8) {
+      mw[q] |= (uint32_t)group_xor<4>((int)mw[q]);
+      pw[q] |= (uint32_t)group_xor<4>((int)pw[q]);
+    }
+    mbits |= (Bits)mw[q] << (32 * q);
+    pbits |= (Bits)pw[q] << (32 * q);
+  }
+  // the extreme key of the masked positions, lowest position on ties
+  float best = 0.f;
+  int bi = 0x7fffffff;
+  if (rule == kMaxConf || rule == kMinConf || rule == kMaxEnt) {
+    const bool lowest = rule == kMinConf;
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float k = kv[4 * q + j];
+        const bool m = (mbits >> pos(q, j)) & 1u;
+        const bool take = m & ((bi == 0x7fffffff) | (lowest ? k < best : k > best));
+        best = take ? k : best;
+        bi = take ? pos(q, j) : bi;
+      }
+    auto combine = [&](float ob, int oi) {
+      const bool better = lowest ? ob < best : ob > best;
+      const bool take =
+          oi != 0x7fffffff && (bi == 0x7fffffff || better || (ob == best && oi < bi));
+      best = take ? ob : best;
+      bi = take ? oi : bi;
+    };
+    combine(__int_as_float(group_xor<1>(__float_as_int(best))), group_xor<1>(bi));
+    combine(__int_as_float(group_xor<2>(__float_as_int(best))), group_xor<2>(bi));
+    if (G == 8) combine(__int_as_float(group_xor<4>(__float_as_int(best))), group_xor<4>(bi));
+  }
+  if (mbits == 0) {  // no block at s, or nothing masked in it: skip forward
+    if (t == 0)
+      lane_rule(b, s >= 0 && s < L ? min(s + BL, L) : s, L, BL, tau, rule, conf, entropy, uniform,
+                argmax, tokens, mask, block_start, fallback, ncommit, my_commits, RowMajor{L});
     return;
   }
-  // Blocks of at most 32 positions whose 32 entries from s stay in the row
-  // and start 16-byte aligned: mask and confidences come in with wide loads
-  // issued together and the decision is taken on a bitmask in registers.
-  if (rule != kMaxEnt && BL <= 32 && s + 32 <= L &&
-      ((reinterpret_cast<uintptr_t>(mask + base + s) | reinterpret_cast<uintptr_t>(conf + base + s)) &
-       15) == 0) {
-    const int cnt = min(BL, L - s);
-    const uint4 mv0 = *reinterpret_cast<const uint4*>(mask + base + s);
-    const uint4 mv1 = *reinterpret_cast<const uint4*>(mask + base + s + 16);
-    float c[32];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const float4 v = *reinterpret_cast<const float4*>(conf + base + s + 4 * q);
-      c[4 * q] = v.x;
-      c[4 * q + 1] = v.y;
-      c[4 * q + 2] = v.z;
-      c[4 * q + 3] = v.w;
+  const bool fb = pbits == 0;
+  Bits commit = pbits;
+  if (fb) {
+    int pick = bi;
+    if (rule == kLeftmost) {
+      pick = low_bit(mbits);
+    } else if (rule == kRandom) {
+      const int n = bit_count(mbits);
+      int j = (int)(uniform[b] * (float)n);
+      j = j > n - 1 ? n - 1 : (j < 0 ? 0 : j);
+      Bits rest = mbits;
+      for (int i = 0; i < j; ++i) rest &= rest - 1;  // drop the j lowest
+      pick = low_bit(rest);
     }
-    const uint32_t mw[8] = {mv0.x, mv0.y, mv0.z, mv0.w, mv1.x, mv1.y, mv1.z, mv1.w};
-    uint32_t mbits = 0, pbits = 0;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-      const bool m = i < cnt && ((mw[i >> 2] >> (8 * (i & 3))) & 0xffu) != 0;
-      mbits |= (uint32_t)m << i;
-      pbits |= (uint32_t)(m && c[i] > tau) << i;
-    }
-    if (mbits != 0) {  // the block at s is the active block
-      const bool fb = pbits == 0;
-      uint32_t commit = pbits;
-      if (fb) {
-        int pick = 0;
-        if (rule == kLeftmost) {
-          pick = __ffs(mbits) - 1;
-        } else if (rule == kRandom) {
-          const int n = __popc(mbits);
-          int j = (int)(uniform[b] * (float)n);
-          j = j > n - 1 ? n - 1 : (j < 0 ? 0 : j);
-          uint32_t rest = mbits;
-          for (int t = 0; t < j; ++t) rest &= rest - 1;  // drop the j lowest
-          pick = __ffs(rest) - 1;
-        } else {
-          const bool lowest = rule == kMinConf;
-          float best = 0.f;
-          int bi = -1;
-#pragma unroll
-          for (int i = 0; i < 32; ++i)
-            if (((mbits >> i) & 1u) && (bi < 0 || (lowest ? c[i] < best : c[i] > best))) {
-              best = c[i];
-              bi = i;
-            }
-          pick = bi;
-        }
-        commit = 1u << pick;
-      }
-      int written = 0;
-      for (uint32_t rest = commit; rest; rest &= rest - 1) {
-        const int k = s + __ffs(rest) - 1;
-        tokens[base + k] = argmax[base + k];
-        mask[base + k] = 0;
-        if (my_commits) my_commits[written] = k;
-        ++written;
-      }
-      if (my_commits)
-        for (int i = written; i < BL; ++i) my_commits[i] = -1;
-      fallback[b] = fb ? 1 : 0;
-      block_start[b] = s;
-      if (ncommit) ncommit[b] = written;
-      return;
-    }
-    s += BL;  // nothing masked there: continue the skip-forward below
+    commit = (Bits)1 << pick;
   }
-  lane_rule(b, s, L, BL, tau, rule, conf, entropy, uniform, argmax, tokens, mask, block_start,
-            fallback, ncommit, my_commits, RowMajor{L});
+  // the candidates all in flight before the first is stored
+  int32_t cand[4 * N];
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if ((commit >> pos(q, j)) & 1u) cand[4 * q + j] = argmax[base + s + pos(q, j)];
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int p = pos(q, j);
+      if ((commit >> p) & 1u) {
+        mask[base + s + p] = 0;
+        if (my_commits) my_commits[bit_count((Bits)(commit & (((Bits)1 << p) - 1)))] = s + p;
+      }
+    }
+  const int written = bit_count(commit);
+  if (my_commits)
+    for (int i = t; i < BL; i += G)
+      if (i >= written) my_commits[i] = -1;
+  if (t == 0) {
+    fallback[b] = fb ? 1 : 0;
+    block_start[b] = s;
+    if (ncommit) ncommit[b] = written;
+  }
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if ((commit >> pos(q, j)) & 1u) tokens[base + s + pos(q, j)] = cand[4 * q + j];
 }
 
 // Position-major state (element (b, k) at k * B + b): one lane per group of
@@ -901,10 +995,16 @@ hipError_t launch_select(int B, int L, int block_len, float tau, int rule,
     else FORK_SELECT_PM(1, 16, false, false);
 #undef FORK_SELECT_PM
   }
-  else if (B >= kLaneSelectMinB && block_len <= kLaneSelectMaxBL)
-    hipLaunchKernelGGL(select_lanes_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0,
-                       stream, B, L, block_len, tau, rule, conf, entropy, uniform, argmax,
-                       tokens, mask, block_start, fallback, ncommit, commit_pos);
+  else if (B >= kGroupSelectMinB && block_len <= kGroupSelectMaxBL) {
+#define FORK_SELECT_GROUP(Q, G)                                                                  \
+  hipLaunchKernelGGL((select_group_kernel<Q, G>), dim3((unsigned)((B + 256 / G - 1) / (256 / G))), \
+                     dim3(256), 0, stream, B, L, block_len, tau, rule, conf, entropy, uniform,   \
+                     argmax, tokens, mask, block_start, fallback, ncommit, commit_pos)
+    if (block_len > 32) FORK_SELECT_GROUP(2, 8);
+    else if (B < kGroupEightMinB) FORK_SELECT_GROUP(1, 4);
+    else FORK_SELECT_GROUP(1, 8);
+#undef FORK_SELECT_GROUP
+  }
   else
     hipLaunchKernelGGL(select_kernel, dim3((unsigned)B), dim3(64), 0, stream, L,
                        block_len, tau, rule, conf, entropy, uniform, argmax, tokens, mask,

@@ -152,6 +152,16 @@ def test_row_major_whole_wave_blocks(B, L, BL, rule, outputs):
                 assert np.all(g[5][b, done.size:] == -1)
 
 
+@pytest.mark.parametrize("L,BL", [(32, 32), (33, 31), (64, 32), (67, 33), (72, 40), (64, 64),
+                                  (131, 63), (200, 64), (9, 5)])
+@pytest.mark.parametrize("rule", [0, 1, 2, 3, 4])
+def test_lane_groups_match_oracle(L, BL, rule):
+    """Blocks around 32 and 64 positions, rows and starts on and off the
+    16-byte grid, blocks cut by the row's end, and a last workgroup that is
+    not full."""
+    _check_against_oracle(4099, L, BL, rule, _binding.FORK_LAYOUT_ROW_MAJOR)
+
+
 def test_lane_and_wave_paths_agree():
     """The first sequences of a large batch (lane path) and the same
     sequences run as a small batch (wave path) give identical results."""
