@@ -55,10 +55,10 @@ hipError_t launch_gemm_stats(const void* hidden, const void* W, bool bf16,
 
 // The same for bf16 with 64, 128 or 256 positions per workgroup; the same
 // partials, bit for bit.  nontemporal: W is loaded past the caches (always for
-// 256 positions).
-hipError_t launch_gemm_narrow(int positions, bool nontemporal, const void* hidden, const void* W,
-                              int M, int d, int V, float4* partials, const int32_t* rowlist,
-                              int Mh, const SampleArgs& sample, const TargetArgs& target,
+// 256 positions); two_per_cu: a shorter W ring (64 positions only).
+hipError_t launch_gemm_narrow(int positions, bool nontemporal, bool two_per_cu,
+                              const void* hidden, const void* W, int M, int d, int V,
+                              float4* partials, const int32_t* rowlist, int Mh, const SampleArgs& sample, const TargetArgs& target,
                               hipStream_t stream);
 
 // launch_gemm_stats for fp32 inputs.

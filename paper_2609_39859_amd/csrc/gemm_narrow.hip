@@ -22,6 +22,11 @@
 //   M = 256: 256 -> 223; M = 256, V = 15808: 79 -> 56; M = 128, V = 2000:
 //   52 -> 36; M = 128, d = 1024, V = 32000: 24.7 -> 19.9; d = 256, V = 2000:
 //   14 -> 9.
+// With more than one round of 64-position tiles a two-slot W ring (80 KiB) puts
+// two workgroups on a CU, so that one's statistics and first loads run under the
+// other's main loop (M = 64, V = 83339, d = 224 / 1024 / 4096: 17.3 / 43.8 / 156
+// -> 15.6 / 39.5 / 143 us); with one round the third slot is worth more (M = 130,
+// V = 9000, d = 4096: 38 against 56 us).
 // Tried and not kept: 128 vocabulary rows per workgroup with two workgroups
 // per CU (equal when W streams, slower otherwise: twice the hidden traffic),
 // four W slots instead of three (equal), loads of W and hidden issued by
@@ -36,19 +41,19 @@
 namespace fork {
 namespace {
 
-template <int NJ, bool kNt, int kMode>
-__global__ __launch_bounds__(64 * kWaves, 2) void gemm_narrow_kernel(
+template <int NJ, bool kNt, int kMode, int WS>
+__global__ __launch_bounds__(64 * kWaves, WS == 2 ? 4 : 2) void gemm_narrow_kernel(
     const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ W, int M, int d,
     int V, int nvt, int npt, float4* __restrict__ partials,
     const int32_t* __restrict__ rowlist, int Mh, SampleArgs sa, TargetArgs ta) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[narrow_lds_bytes(NJ)];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[narrow_lds_bytes(NJ, WS)];
   int vt, pt;
   map_tile(blockIdx.x, nvt * npt, nvt, npt, vt, pt);
-  gemm_narrow_body<NJ, kNt, kMode>(smem, hidden, W, M, d, V, vt, pt * 64 * NJ, partials, rowlist,
-                                   Mh, sa, ta);
+  gemm_narrow_body<NJ, kNt, kMode, WS>(smem, hidden, W, M, d, V, vt, pt * 64 * NJ, partials,
+                                       rowlist, Mh, sa, ta);
 }
 
-template <int NJ, bool kNt>
+template <int NJ, bool kNt, int WS>
 hipError_t launch(const void* hidden, const void* W, int M, int d, int V, float4* partials,
                   const int32_t* rowlist, int Mh, const SampleArgs& sample,
                   const TargetArgs& target, hipStream_t stream) {
@@ -58,8 +63,8 @@ hipError_t launch(const void* hidden, const void* W, int M, int d, int V, float4
   const auto* h = static_cast<const unsigned char*>(hidden);
   const auto* w = static_cast<const unsigned char*>(W);
 #define FORK_LAUNCH(MODE)                                                                        \
-  hipLaunchKernelGGL((gemm_narrow_kernel<NJ, kNt, MODE>), grid, block, 0, stream, h, w, M, d, V, \
-                     nvt, npt, partials, rowlist, Mh, sample, target)
+  hipLaunchKernelGGL((gemm_narrow_kernel<NJ, kNt, MODE, WS>), grid, block, 0, stream, h, w, M, d, \
+                     V, nvt, npt, partials, rowlist, Mh, sample, target)
   if (target.token)
     FORK_LAUNCH(kTarget);
   else if (sample.row)
@@ -72,15 +77,17 @@ hipError_t launch(const void* hidden, const void* W, int M, int d, int V, float4
 
 }  // namespace
 
-hipError_t launch_gemm_narrow(int positions, bool nontemporal, const void* hidden, const void* W,
-                              int M, int d, int V, float4* partials, const int32_t* rowlist,
-                              int Mh, const SampleArgs& sample, const TargetArgs& target,
+hipError_t launch_gemm_narrow(int positions, bool nontemporal, bool two_per_cu,
+                              const void* hidden, const void* W, int M, int d, int V,
+                              float4* partials, const int32_t* rowlist, int Mh, const SampleArgs& sample, const TargetArgs& target,
                               hipStream_t stream) {
-#define FORK_NARROW(NJ, NT) \
-  launch<NJ, NT>(hidden, W, M, d, V, partials, rowlist, Mh, sample, target, stream)
-  if (positions == 64) return nontemporal ? FORK_NARROW(1, true) : FORK_NARROW(1, false);
-  if (positions == 128) return nontemporal ? FORK_NARROW(2, true) : FORK_NARROW(2, false);
-  return FORK_NARROW(4, true);
+#define FORK_NARROW(NJ, NT, WS) \
+  launch<NJ, NT, WS>(hidden, W, M, d, V, partials, rowlist, Mh, sample, target, stream)
+  if (positions == 64 && two_per_cu)
+    return nontemporal ? FORK_NARROW(1, true, 2) : FORK_NARROW(1, false, 2);
+  if (positions == 64) return nontemporal ? FORK_NARROW(1, true, 3) : FORK_NARROW(1, false, 3);
+  if (positions == 128) return nontemporal ? FORK_NARROW(2, true, 3) : FORK_NARROW(2, false, 3);
+  return FORK_NARROW(4, true, 3);
 #undef FORK_NARROW
 }
 

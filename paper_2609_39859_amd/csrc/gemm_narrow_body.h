@@ -8,17 +8,18 @@ namespace fork {
 namespace {
 
 constexpr int kWaves = 8;                   // 2 vocabulary halves x 4 position quarters
-constexpr int kWSlots = 3;                  // W ring; the hidden ring is one shorter
-constexpr int kHSlots = kWSlots - 1;
+constexpr int kHSlots = 2;                  // hidden ring
 constexpr int kNontemporal = 2;             // cache policy bits of a buffer load
 
-constexpr int narrow_lds_bytes(int NJ) {
-  return kWSlots * kOperandBytes + kHSlots * 64 * NJ * kSlab;
+constexpr int narrow_lds_bytes(int NJ, int WS) {
+  return WS * kOperandBytes + kHSlots * 64 * NJ * kSlab;
 }
 
 // One workgroup of 512 threads: vocabulary tile vt, positions p0 .. p0 + 64 NJ,
-// smem of narrow_lds_bytes(NJ).
-template <int NJ, bool kNt, int kMode>
+// W ring of WS = 3 slots (W two stages ahead of its use) or 2 (one stage, with
+// 80 KiB for NJ = 1, so that two workgroups share a CU), smem of
+// narrow_lds_bytes(NJ, WS).
+template <int NJ, bool kNt, int kMode, int WS>
 __device__ __forceinline__ void gemm_narrow_body(
     unsigned char* smem, const unsigned char* __restrict__ hidden,
     const unsigned char* __restrict__ W, int M, int d, int V, int vt, int p0,
@@ -92,7 +93,7 @@ __device__ __forceinline__ void gemm_narrow_body(
   auto issue_H1 = [&](int s, int slot, int q) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
         rsH,
-        (__attribute__((address_space(3))) void*)(smem + kWSlots * kOperandBytes + slot * kHBytes +
+        (__attribute__((address_space(3))) void*)(smem + WS * kOperandBytes + slot * kHBytes +
                                                   (wave * LH + q) * 1024),
         16, at(hoff[q], s, wave * LH + q), 0, 0, 0);
   };
@@ -115,7 +116,7 @@ __device__ __forceinline__ void gemm_narrow_body(
                                             (((2 * kq + kk) ^ fx) << 4));
   };
   auto rd_b = [&](int slot, int kk, int j) {
-    return *reinterpret_cast<const bf16x8*>(smem + kWSlots * kOperandBytes + slot * kHBytes +
+    return *reinterpret_cast<const bf16x8*>(smem + WS * kOperandBytes + slot * kHBytes +
                                             (wp * kWaveP + fr + 16 * j) * kSlab +
                                             (((2 * kq + kk) ^ fx) << 4));
   };
@@ -139,9 +140,10 @@ __device__ __forceinline__ void gemm_narrow_body(
       for (int j = 0; j < NJ; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     };
-    // Load order W0 H0 W1 H1, then per stage k: W(k + 2) in the first step,
-    // H(k + 2) in the second, after the stage's barrier.  At that barrier only
-    // W(k + 2) may be in flight; every slot refilled after it belongs to a
+    // Load order W0 H0 W1 H1, then per stage k: W(k + 2) in the first step
+    // (WS = 3), H(k + 2) (WS = 2: and W(k + 2)) in the second, after the stage's
+    // barrier.  At that barrier only W(k + 2) (WS = 2: nothing) may be in
+    // flight; every slot refilled after it belongs to a
     // stage whose fragments all waves have read.
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -160,7 +162,7 @@ __device__ __forceinline__ void gemm_narrow_body(
     }
     int ws = 0, hs = 0, ws2 = 2;  // W slots of stages k and k + 2, hidden slot of k
     for (int k = 0; k < nk; ++k) {
-      const int ws1 = ws == 2 ? 0 : ws + 1, hs1 = hs ^ 1;
+      const int ws1 = ws == WS - 1 ? 0 : ws + 1, hs1 = hs ^ 1;
       // first step; after the MFMAs of row i its fragment is refilled for the
       // second step
 #pragma unroll
@@ -170,7 +172,7 @@ __device__ __forceinline__ void gemm_narrow_body(
           a[i] = rd_a(ws, 1, i);
           if (i < NJ) b1[i] = rd_b(hs, 1, i);
         }
-        if (i & 1) issue_W1(k + 2, ws2, i >> 1);
+        if (WS == 3 && (i & 1)) issue_W1(k + 2, ws2, i >> 1);
       }
       if (kLive) {
 #pragma unroll
@@ -178,7 +180,7 @@ __device__ __forceinline__ void gemm_narrow_body(
           __builtin_amdgcn_sched_group_barrier(0x008, NJ, 0);  // MFMA
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
           if (i < NJ) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          if (i & 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // buffer load
+          if (WS == 3 && (i & 1)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // load
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -189,7 +191,7 @@ __device__ __forceinline__ void gemm_narrow_body(
         mfma_row(1, b1);
       }
       __builtin_amdgcn_sched_barrier(0);
-      wait_vm_lgkm0<LW>();
+      wait_vm_lgkm0<WS == 3 ? LW : 0>();
       barrier_nofence();
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -200,6 +202,7 @@ __device__ __forceinline__ void gemm_narrow_body(
           if (i < 4) a[i - 2] = rd_a(ws1, 0, i - 2);
           if (i >= 4 && i - 4 < NJ) b0[i - 4] = rd_b(hs1, 0, i - 4);
         }
+        if (WS == 2 && i - 2 < LW) issue_W1(k + 2, ws, i - 2);
         if (i - 2 < LH) issue_H1(k + 2, hs, i - 2);
       }
       if (kLive) {
@@ -208,6 +211,7 @@ __device__ __forceinline__ void gemm_narrow_body(
           __builtin_amdgcn_sched_group_barrier(0x008, NJ, 0);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
           if (i < 4 || i - 4 < NJ) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          if (WS == 2 && i - 2 < LW) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
           if (i - 2 < LH) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         }
       }

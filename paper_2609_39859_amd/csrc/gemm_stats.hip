@@ -145,7 +145,7 @@ __device__ __forceinline__ void gemm_stats_bf16_body(
     tile_of(nbig + (quarter >> 2), nvt, npt, vt, pt);
     const int p0 = pt * kTileP + (quarter & 3) * 64;
     if (p0 < M)
-      gemm_narrow_body<1, false, kMode>(smem, hidden, W, M, d, V, vt, p0, partials, rowlist, Mh,
+      gemm_narrow_body<1, false, kMode, 3>(smem, hidden, W, M, d, V, vt, p0, partials, rowlist, Mh,
                                         sa, ta);
     return;
   }
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(kThreads) void gemm_stats_bf16_draw_ilv_kernel(FORK
 struct TileChoice {
   bool narrow;
   int positions;
-  bool nontemporal;
+  bool nontemporal, two_per_cu;
 };
 
 constexpr long long kCus = 256;
@@ -498,8 +498,8 @@ TileChoice choose_tile(int M, int d, int V) {
   // (M = 256, V = 126464: 239 against 223 us; 412 MB 92 against 94 us).
   const long long bytes = 2LL * V * d;
   const bool nt = tiles(best) == 1 && bytes > (320LL << 20);
-  if (best == 256 && !(nt && bytes > (512LL << 20))) return {false, 256, false};
-  return {true, best, nt};
+  if (best == 256 && !(nt && bytes > (512LL << 20))) return {false, 256, false, false};
+  return {true, best, nt, best == 64 && nvt * tiles(64) > kCus};
 }
 
 }  // namespace
@@ -512,8 +512,8 @@ hipError_t launch_gemm_stats(const void* hidden, const void* W, bool bf16, int M
     return launch_gemm_f32(hidden, W, M, d, V, partials, rowlist, Mh, sample, target, stream);
   const TileChoice t = choose_tile(M, d, V);
   if (t.narrow)
-    return launch_gemm_narrow(t.positions, t.nontemporal, hidden, W, M, d, V, partials, rowlist,
-                              Mh, sample, target, stream);
+    return launch_gemm_narrow(t.positions, t.nontemporal, t.two_per_cu, hidden, W, M, d, V, partials,
+                              rowlist, Mh, sample, target, stream);
   const int nvt = num_vocab_tiles(V);
   const int npt = num_pos_tiles(M);
   const bool draw = sample.row != nullptr;
