@@ -44,10 +44,12 @@ def build(verbose: bool = False) -> str:
     example that drives one step through the C ABI; returns the path of
     libforkstep.so."""
     fast = build_fastcall(verbose)
-    _build_lib(PROBE_LIB, PROBE_SOURCES, verbose)
-    lib = _build_lib(LIB, SOURCES, verbose)
-    build_c_example(verbose)
-    _finish(fast)
+    try:
+        _build_lib(PROBE_LIB, PROBE_SOURCES, verbose)
+        lib = _build_lib(LIB, SOURCES, verbose)
+        build_c_example(verbose)
+    finally:
+        _finish(fast)
     return lib
 
 
@@ -78,6 +80,8 @@ def build_fastcall(verbose: bool = False):
 def _finish(job) -> None:
     p, tmp = job
     if p.wait():
+        if os.path.exists(tmp):
+            os.remove(tmp)
         raise RuntimeError("g++ failed for fastcall.cpp")
     os.replace(tmp, FASTCALL)
 

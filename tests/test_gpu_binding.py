@@ -106,3 +106,21 @@ def test_native_calls_match_the_bindings_own(monkeypatch, name):
                 assert a == b, (k, change.__name__)
             else:
                 assert all(torch.equal(a[n], b[n]) for n in a), (k, change.__name__)
+
+
+@pytest.mark.parametrize("name", ["step", "noalloc", "logprob"])
+def test_native_calls_take_the_lm_head_events(name):
+    """The pair of events is recorded by the native call, around the LM head;
+    a pair of another form is left to the binding."""
+    fn, kw = dict(_calls())[name]
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()
+    pair = tuple(e.cuda_event for e in ev)
+    for events in (pair, list(pair)):
+        begin = torch.cuda.Event(enable_timing=True)
+        begin.record()
+        fn(**kw, events=events)
+        torch.cuda.synchronize()
+        assert begin.elapsed_time(ev[0]) >= 0
+        assert ev[0].elapsed_time(ev[1]) > 0
