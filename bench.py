@@ -49,7 +49,8 @@ METRIC = "denoising steps/sec and positions/sec at B·L×4096×126464; % MFMA bf
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_lmhead_llada8b.json")
-LMHEAD_SRC = os.path.join(ROOT, "paper_2609_39859_amd", "csrc", "gemm_stats.hip")
+LMHEAD_SRCS = [os.path.join(ROOT, "paper_2609_39859_amd", "csrc", name) for name in
+               ("lmhead_device.h", "gemm_stats.hip", "gemm_narrow_body.h", "gemm_narrow.hip")]
 
 
 def _hip():
@@ -66,8 +67,11 @@ def _hip():
 
 
 def _source_hash():
-    with open(LMHEAD_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for path in LMHEAD_SRCS:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def _traffic_per_launch(kernel):
@@ -797,8 +801,8 @@ def main():
             "graph_ms_per_step": sb.graph_timed(args.steps, _binding.FORK_ROWS_ACTIVE),
             "roofline": {"bound": "hbm", "achieved": a_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                          "frac": a_gbs / PEAK_HBM_GBS,
-                         "traffic": _traffic_per_launch("gemm_stats_bf16_rows_kernel"),
-                         "kernel": "gemm_stats_bf16_rows_kernel (LM head on the active rows)",
+                         "traffic": _traffic_per_launch("gemm_narrow_kernel greedy"),
+                         "kernel": "gemm_narrow_kernel (LM head on the active rows)",
                          "algorithmic_bytes_per_launch": a_bytes,
                          "mfma_frac": 2.0 * Ma * d * V / (a_lm_ms * 1e-3) / 1e12
                                       / PEAK_BF16_TFLOPS}}
@@ -818,7 +822,7 @@ def main():
         drawn = {"temperature": 0.8}
         for label, mode, kernel in (("all_rows", _binding.FORK_ROWS_ALL, "gemm_stats_bf16_draw_ilv_kernel"),
                                     ("active_rows", _binding.FORK_ROWS_ACTIVE,
-                                     "gemm_stats_bf16_rows_draw_kernel")):
+                                     "gemm_narrow_kernel drawn")):
             print("bench: timing %d steps, drawn candidates, %s" % (args.steps, label),
                   file=sys.stderr, flush=True)
             d_total, d_lm, _ = sb.timed(mode, args.steps, args.warmup, temperature=0.8)
