@@ -617,17 +617,23 @@ __global__ __launch_bounds__(256) void select_group_kernel(
     mbits |= (Bits)mw[q] << (32 * q);
     pbits |= (Bits)pw[q] << (32 * q);
   }
-  // the extreme key of the masked positions, lowest position on ties
+  // the extreme key of the masked positions, lowest position on ties.  A scan
+  // in order keeps a NaN at the first masked position and takes no other: the
+  // first counts as the extreme value, the others are left out, so that the
+  // lanes compare ordered keys only and all end with the same position.
   float best = 0.f;
   int bi = 0x7fffffff;
   if (rule == kMaxConf || rule == kMinConf || rule == kMaxEnt) {
     const bool lowest = rule == kMinConf;
+    const int first = low_bit(mbits);
 #pragma unroll
     for (int q = 0; q < N; ++q)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float k = kv[4 * q + j];
-        const bool m = (mbits >> pos(q, j)) & 1u;
+        const float v = kv[4 * q + j];
+        const bool nan = v != v;
+        const float k = nan ? (lowest ? -INFINITY : INFINITY) : v;
+        const bool m = ((mbits >> pos(q, j)) & 1u) && (!nan || pos(q, j) == first);
         const bool take = m & ((bi == 0x7fffffff) | (lowest ? k < best : k > best));
         best = take ? k : best;
         bi = take ? pos(q, j) : bi;

@@ -162,6 +162,52 @@ def test_lane_groups_match_oracle(L, BL, rule):
     _check_against_oracle(4099, L, BL, rule, _binding.FORK_LAYOUT_ROW_MAJOR)
 
 
+def _check_whole(state, B, L, BL, rule, tau, layout=_binding.FORK_LAYOUT_ROW_MAJOR):
+    """Every output against the oracle, the committed positions of all
+    sequences at once."""
+    conf, ent, am, tok, msk, bs, uni = state
+    g = _run(conf, ent, am, tok, msk, bs, uni, B, L, BL, tau, rule, layout)
+    o = oracle.select_ex(conf, am, tok, msk, bs, B, L, BL, float(np.float32(tau)), rule,
+                         entropy=ent, uniform=uni)
+    for k, (x, y) in enumerate(zip(g[:5], o)):
+        assert np.array_equal(x, y), ("tokens", "mask", "block_start", "fallback", "ncommit")[k]
+    done = (msk != o[1]).reshape(B, L)
+    want = np.full((B, BL), -1, np.int32)
+    seq, where = np.nonzero(done)
+    want[seq, (np.cumsum(done, axis=1) - 1)[seq, where]] = where
+    assert np.array_equal(g[5], want)
+
+
+def _nan_state(B, L, BL, rule):
+    """Keys without a value above the threshold: NaN at the first masked
+    position of the block, at random positions, and at all of them."""
+    conf, ent, am, tok, msk, bs, uni = _state(B, L, 1000, B + 13 * L + BL + rule)
+    conf = np.round(conf * 0.5, 2)                          # frequent ties
+    rng = np.random.default_rng(B + L)
+    bs[: B // 2] = rng.integers(0, L - BL + 1, B // 2)      # half the blocks whole
+    key = (ent if rule == 3 else conf).reshape(B, L)
+    m = msk.reshape(B, L)
+    for b in range(min(B, 4200)):
+        at = bs[b] + np.nonzero(m[b, bs[b]:])[0]
+        if b % 3 == 0:
+            key[b, at[:1]] = np.nan
+        elif b % 3 == 1:
+            key[b, rng.random(L) < 0.3] = np.nan
+        else:
+            key[b] = np.nan
+    return conf, ent, am, tok, msk, bs, uni
+
+
+@pytest.mark.parametrize("B,L,BL", [(4099, 32, 32), (4099, 67, 31), (4099, 64, 64), (4099, 131, 40),
+                                    ((1 << 18) + 3, 32, 32), ((1 << 18) + 3, 37, 20)])
+@pytest.mark.parametrize("rule", [1, 2, 3])
+def test_nan_keys_follow_the_scan_in_order(B, L, BL, rule):
+    """Four and eight lanes per sequence, blocks up to 32 and up to 64
+    positions: one position is committed, the one a scan in order picks."""
+    _need_gpu()
+    _check_whole(_nan_state(B, L, BL, rule), B, L, BL, rule, 0.9)
+
+
 def test_lane_and_wave_paths_agree():
     """The first sequences of a large batch (lane path) and the same
     sequences run as a small batch (wave path) give identical results."""
