@@ -247,7 +247,11 @@ __global__ __launch_bounds__(64) void select_kernel(
         // lowest position on ties
         const bool lowest = rule == kMinConf;
         float best = masked ? (rule == kMaxEnt ? entropy[base + k] : cf) : 0.f;
-        int bi = masked ? k : 0x7fffffff;
+        // as in a scan in order, a NaN counts only at the first masked position
+        const bool nan = best != best;
+        const bool in = masked && (!nan || k == s + __ffsll((long long)mball) - 1);
+        if (nan) best = lowest ? -INFINITY : INFINITY;
+        int bi = in ? k : 0x7fffffff;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
           const float ob = __shfl_xor(best, off);
@@ -355,12 +359,17 @@ __global__ __launch_bounds__(64) void select_kernel(
       const float* key = rule == kMaxEnt ? entropy : conf;
       const bool lowest = rule == kMinConf;
       float best = 0.f;
-      int bi = 0x7fffffff;
+      int bi = 0x7fffffff, first = -1;
       for (int c = s; c < e; c += 64) {
         const int k = c + lane;
-        if (k < e && mask[base + k] != 0) {
-          const float v = key[base + k];
-          if (bi == 0x7fffffff || (lowest ? v < best : v > best)) {
+        const bool masked = k < e && mask[base + k] != 0;
+        const unsigned long long bm = ballot(masked);
+        if (first < 0 && bm) first = c + __ffsll((long long)bm) - 1;
+        if (masked) {
+          float v = key[base + k];
+          const bool nan = v != v;  // counts only at the first masked position
+          if (nan) v = lowest ? -INFINITY : INFINITY;
+          if ((!nan || k == first) && (bi == 0x7fffffff || (lowest ? v < best : v > best))) {
             best = v;
             bi = k;
           }

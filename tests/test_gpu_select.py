@@ -208,6 +208,17 @@ def test_nan_keys_follow_the_scan_in_order(B, L, BL, rule):
     _check_whole(_nan_state(B, L, BL, rule), B, L, BL, rule, 0.9)
 
 
+@pytest.mark.parametrize("B,L,BL", [(60, 64, 64), (60, 67, 31), (60, 65, 65), (60, 400, 150)])
+@pytest.mark.parametrize("layout", [_binding.FORK_LAYOUT_ROW_MAJOR,
+                                    _binding.FORK_LAYOUT_POSITION_MAJOR])
+@pytest.mark.parametrize("rule", [1, 2, 3])
+def test_nan_keys_in_small_batches(B, L, BL, layout, rule):
+    """One wave per sequence, blocks up to 64 positions and longer, and the
+    position-major kernel."""
+    _need_gpu()
+    _check_whole(_nan_state(B, L, BL, rule), B, L, BL, rule, 0.9, layout)
+
+
 def test_lane_and_wave_paths_agree():
     """The first sequences of a large batch (lane path) and the same
     sequences run as a small batch (wave path) give identical results."""
