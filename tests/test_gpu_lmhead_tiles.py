@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2609_39859_amd import _binding
-from harness import Report, compare_stats, gpu_step, host_bits, record
+from harness import Report, compare_sampled, compare_stats, gpu_step, host_bits, record
 
 pytestmark = pytest.mark.gpu
 
@@ -53,6 +53,22 @@ def test_f32_tile_edges_match_oracle(M, d, V):
     rep = Report()
     compare_stats(g, ref, np.arange(M), host_bits(h), host_bits(W), d, rep)
     record(rep, "tiles_f32")
+
+
+# a ragged vocabulary tile: its last block, half and row, one row in all
+@pytest.mark.parametrize("V", [1, 15, 17, 127, 128, 130, 255, 300])
+@pytest.mark.parametrize("M,dtype", [(70, torch.bfloat16), (700, torch.bfloat16),
+                                     (70, torch.float32)])
+def test_drawn_candidates_of_a_ragged_tile(V, M, dtype):
+    d, rows = 72, np.arange(70)
+    h, W = _inputs(M, d, V, M + V, dtype)
+    g = _step(h, W, 0.8)
+    hb, Wb = host_bits(h), host_bits(W)
+    st = oracle.row_stats(hb, Wb, rows)
+    sm = oracle.row_sample(hb, Wb, rows, 0.8, 11, 2)
+    rep = Report()
+    compare_sampled(g, st, sm, rows, hb, Wb, d, 0.8, 11, 2, rep)
+    record(rep, "tiles_drawn")
 
 
 # V = 32000 (125 vocabulary tiles): 1024 rows take tiles of 256 positions, 160
