@@ -11,8 +11,8 @@
 //   m   = max_v z_v                 idx = lowest v attaining m
 //   s   = sum_v exp(z_v - m)        t   = sum_v exp(z_v - m) * (z_v - m)
 //
-// This file: the bf16 kernel with 256 positions per workgroup, and the choice
-// of the kernel of a launch.  Fewer positions per workgroup are in
+// This file: the bf16 kernel with 256 positions per workgroup, and the launch
+// (the choice of its kernel: lmhead_tiles.h).  Fewer positions per workgroup are in
 // gemm_narrow.hip, fp32 inputs in gemm_f32.hip.
 //
 // Work decomposition (gfx950 / CDNA4):
@@ -52,6 +52,7 @@
 // counter (v / 4, row, step counter, 0): one generator call serves the four
 // consecutive vocabulary entries a lane holds in one accumulator group.
 #include "gemm_narrow_body.h"
+#include "lmhead_tiles.h"
 
 namespace fork {
 namespace {
@@ -448,60 +449,6 @@ __global__ __launch_bounds__(kThreads) void gemm_stats_bf16_draw_ilv_kernel(FORK
 #undef FORK_GEMM_ARGS
 #undef FORK_GEMM_ENTRIES
 
-// Positions per workgroup of the bf16 LM head.  A tile of 64, 128 or 256
-// positions takes 1 : 1.45 : 2.1 (measured over d = 256 .. 4096, V = 2000 ..
-// 32000, one round of tiles: 9.4 / 12.2 / 16.2 us, 14.3 / 19.9 / 27.5 us,
-// 36.5 / 53 / 73 us; with every CU busy 39 / 58 / 94 us), and the 256 CUs take
-// one tile each per round, so the cost of a launch is the rounds times the
-// tile's.  Rows that are not whole cache lines make the smaller tiles, which
-// load more per flop, dearer once more than one round runs (d = 3504, M =
-// 1294, V = 23341: 392 / 257 / 228 us).  Examples (us, 64 / 128 / 256
-// positions): V = 8000, d = 1024: M = 512 16 / 22 / 28, M = 1024 28 / 23 / 29;
-// V = 32000, d = 1024: M = 128 20 / 24 / 25, M = 256 30 / 27 / 30, M = 1024
-// 98 / 79 / 63.  Over 370 such shapes the choice loses 0.3% on the best of the
-// three.
-struct TileChoice {
-  bool narrow;
-  int positions;
-  bool nontemporal, two_per_cu;
-};
-
-constexpr long long kCus = 256;
-
-// Tiles of 256 positions left in a last round that takes at most a quarter of
-// the CUs after a few whole rounds: such tiles run as four workgroups of 64
-// positions each, at the end of the same launch, so that they start on the
-// CUs that finish first (M = 903, d = 1544, V = 50257, 788 tiles: step 192 ->
-// 180 us; in a launch of their own 190).  Kernels with this path run their
-// 256-position tiles 4% slower than those without, so it pays for at most six
-// rounds.  0 if there are none.
-int tail_tiles(long long n) {
-  const long long rem = n % kCus, full = n / kCus;
-  return full >= 1 && full <= 6 && rem > 0 && rem <= kCus / 4 ? (int)rem : 0;
-}
-
-TileChoice choose_tile(int M, int d, int V) {
-  const long long nvt = num_vocab_tiles(V);
-  auto tiles = [&](int p) { return ((long long)M + p - 1) / p; };
-  auto cost = [&](int p, int per_round) {
-    const long long n = nvt * tiles(p);
-    const bool dear = p < kTileP && n > kCus && d % 64 != 0;
-    return (n + kCus - 1) / kCus * per_round * (dear ? 12 : 10);
-  };
-  const long long c64 = cost(64, 100), c128 = cost(128, 145);
-  const long long c256 = cost(256, 210) - (tail_tiles(nvt * tiles(256)) ? 1050 : 0);
-  const int best = c256 < c64 && c256 < c128 ? 256 : c128 < c64 ? 128 : 64;
-  // One position tile reads W once: past the 256 MB last-level cache it is
-  // loaded nontemporally (M = 64, d = 4096, one W for every step: 130 MB 37 us
-  // cached and 51 nontemporal, 262 MB 52 and 60, 412 MB 80 and 73).  With 256
-  // positions the same holds for the narrow kernel's four-column variant
-  // (M = 256, V = 126464: 239 against 223 us; 412 MB 92 against 94 us).
-  const long long bytes = 2LL * V * d;
-  const bool nt = tiles(best) == 1 && bytes > (320LL << 20);
-  if (best == 256 && !(nt && bytes > (512LL << 20))) return {false, 256, false, false};
-  return {true, best, nt, best == 64 && nvt * tiles(64) > kCus};
-}
-
 }  // namespace
 
 hipError_t launch_gemm_stats(const void* hidden, const void* W, bool bf16, int M, int d, int V,
@@ -510,7 +457,7 @@ hipError_t launch_gemm_stats(const void* hidden, const void* W, bool bf16, int M
                              hipStream_t stream) {
   if (!bf16)
     return launch_gemm_f32(hidden, W, M, d, V, partials, rowlist, Mh, sample, target, stream);
-  const TileChoice t = choose_tile(M, d, V);
+  const TileChoice t = choose_tile(M, d, num_vocab_tiles(V), whole_lines(W, d), 2LL * V * d);
   if (t.narrow)
     return launch_gemm_narrow(t.positions, t.nontemporal, t.two_per_cu, hidden, W, M, d, V, partials,
                               rowlist, Mh, sample, target, stream);
