@@ -59,6 +59,7 @@ __global__ __launch_bounds__(kGrpoThreads) void grpo_group_kernel(
     float* __restrict__ rollout_obj, float* __restrict__ group_obj,
     uint8_t* __restrict__ skipped) {
   __shared__ float red[kGrpoWaves];
+  __shared__ int differ[kGrpoWaves];
   __shared__ float ro[kMaxGroupSize];
   const int g = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -74,13 +75,25 @@ __global__ __launch_bounds__(kGrpoThreads) void grpo_group_kernel(
     n1 = min(max(offsets[i + 1], n0), n);
     if (n0 + lane < n1) d0 = lp_new[n0 + lane] - lp_old[n0 + lane];
   }
+  // Equal rewards have std 0 whatever the rounding of their sum: the mean of 9
+  // or of 512 times 0.1 in binary32 is not 0.1.
   float s = 0.f;
-  for (int j = tid; j < G; j += kGrpoThreads) s += r[j];
+  bool equal = true;
+  const float r0 = r[0];
+  for (int j = tid; j < G; j += kGrpoThreads) {
+    s += r[j];
+    equal &= r[j] == r0;
+  }
+  const unsigned long long unequal = __ballot(!equal);
+  if (lane == 0) differ[w] = unequal != 0;
   const float mean = block_sum<kGrpoWaves>(s, red) / (float)G;
   float q = 0.f;
   for (int j = tid; j < G; j += kGrpoThreads) q += (r[j] - mean) * (r[j] - mean);
   const float sd = sqrtf(block_sum<kGrpoWaves>(q, red) / (float)G);
-  const bool skip = !(sd > 0.f);
+  int any = 0;
+#pragma unroll
+  for (int k = 0; k < kGrpoWaves; ++k) any |= differ[k];
+  const bool skip = !(sd > 0.f) || !any;
 
   // one wave per rollout, lanes over its entries
   for (int j = w; j < G; j += kGrpoWaves) {

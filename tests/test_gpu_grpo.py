@@ -149,6 +149,28 @@ def _compare_objective(g, ref):
     assert g["J"] == pytest.approx(ref["J"], abs=OBJ_TOL, rel=OBJ_TOL)
 
 
+@pytest.mark.parametrize("G", [1, 2, 3, 9, 64, 65, 100, 257, 512, 1000, 1024])
+def test_groups_of_equal_rewards_are_skipped(G):
+    """std 0 whatever the rounding of the rewards' sum; a group in which one
+    reward is the next number up is not skipped."""
+    _need_gpu()
+    rng = np.random.default_rng(G)
+    value = np.concatenate([[0.1, 0.7, 0.3, -0.2], rng.random(12) * 3]).astype(np.float32)
+    rewards = np.repeat(value[:, None], G, axis=1)
+    if G > 1:
+        rewards[::4, G // 2] = np.nextafter(value[::4], np.float32(9))
+    R = rewards.size
+    old = -rng.random(R)
+    lp = (old.astype(np.float32), (old + 0.1 * rng.standard_normal(R)).astype(np.float32))
+    g = _objective(rewards.ravel(), np.arange(R + 1), lp[1], lp[0], G, 0.2)
+    want = np.ones(16, np.uint8)
+    if G > 1:
+        want[::4] = 0
+    assert np.array_equal(g["skipped"], want)
+    off = want == 1
+    assert np.all(g["adv"].reshape(16, G)[off] == 0) and np.all(g["group_obj"][off] == 0)
+
+
 def test_objective_hand_worked_fixture():
     _need_gpu()
     with open(os.path.join(GOLDEN, "grpo_worked.json")) as f:
