@@ -21,14 +21,6 @@
 namespace fork {
 namespace {
 
-// One wave per rollout of a group of 16 and one round of loads per rollout of
-// 64 entries: the launch is bound by its chain of dependent loads and
-// reductions, so a rollout's offsets and first entries are loaded before the
-// advantages, which need two reductions over the workgroup, are known.
-// Measured for 16 groups x 16 rollouts x 15 entries: 6.6 us with four waves
-// and every load in its turn, 4.9 us so (64 x 64 x 100: 21.4 and 10.4 us).
-constexpr int kGrpoThreads = 1024;
-constexpr int kGrpoWaves = kGrpoThreads / 64;
 constexpr int kBatchThreads = 256;
 
 __device__ __forceinline__ float wave_sum(float x) {
@@ -52,14 +44,19 @@ __device__ __forceinline__ float block_sum(float x, float* red) {
   return s;
 }
 
-__global__ __launch_bounds__(kGrpoThreads) void grpo_group_kernel(
+// One workgroup of kWaves waves per group, one wave per rollout at a time.  The
+// launch is bound by its chain of dependent loads and reductions, so a
+// rollout's offsets and first 64 entries are loaded before the advantages,
+// which need two reductions over the workgroup, are known.
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void grpo_group_kernel(
     int G, int n, const float* __restrict__ rewards, const int32_t* __restrict__ offsets,
     const float* __restrict__ lp_new, const float* __restrict__ lp_old, float eps,
     float* __restrict__ adv, float* __restrict__ ratio, float* __restrict__ term,
     float* __restrict__ rollout_obj, float* __restrict__ group_obj,
     uint8_t* __restrict__ skipped) {
-  __shared__ float red[kGrpoWaves];
-  __shared__ int differ[kGrpoWaves];
+  __shared__ float red[kWaves];
+  __shared__ int differ[kWaves];
   __shared__ float ro[kMaxGroupSize];
   const int g = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -80,23 +77,23 @@ __global__ __launch_bounds__(kGrpoThreads) void grpo_group_kernel(
   float s = 0.f;
   bool equal = true;
   const float r0 = r[0];
-  for (int j = tid; j < G; j += kGrpoThreads) {
+  for (int j = tid; j < G; j += 64 * kWaves) {
     s += r[j];
     equal &= r[j] == r0;
   }
   const unsigned long long unequal = __ballot(!equal);
   if (lane == 0) differ[w] = unequal != 0;
-  const float mean = block_sum<kGrpoWaves>(s, red) / (float)G;
+  const float mean = block_sum<kWaves>(s, red) / (float)G;
   float q = 0.f;
-  for (int j = tid; j < G; j += kGrpoThreads) q += (r[j] - mean) * (r[j] - mean);
-  const float sd = sqrtf(block_sum<kGrpoWaves>(q, red) / (float)G);
+  for (int j = tid; j < G; j += 64 * kWaves) q += (r[j] - mean) * (r[j] - mean);
+  const float sd = sqrtf(block_sum<kWaves>(q, red) / (float)G);
   int any = 0;
 #pragma unroll
-  for (int k = 0; k < kGrpoWaves; ++k) any |= differ[k];
+  for (int k = 0; k < kWaves; ++k) any |= differ[k];
   const bool skip = !(sd > 0.f) || !any;
 
   // one wave per rollout, lanes over its entries
-  for (int j = w; j < G; j += kGrpoWaves) {
+  for (int j = w; j < G; j += kWaves) {
     const size_t i = (size_t)g * G + j;
     const float A = skip ? 0.f : (r[j] - mean) / sd;
     if (j != w) {
@@ -122,8 +119,8 @@ __global__ __launch_bounds__(kGrpoThreads) void grpo_group_kernel(
   }
   __syncthreads();
   float t = 0.f;
-  for (int j = tid; j < G; j += kGrpoThreads) t += ro[j];
-  const float gsum = block_sum<kGrpoWaves>(t, red);
+  for (int j = tid; j < G; j += 64 * kWaves) t += ro[j];
+  const float gsum = block_sum<kWaves>(t, red);
   if (tid == 0) {
     group_obj[g] = skip ? 0.f : gsum / (float)G;
     skipped[g] = skip ? 1 : 0;
@@ -236,10 +233,23 @@ hipError_t launch_grpo_objective(int n_groups, int G, int n, const float* reward
                                  const float* lp_old, float eps, float* adv, float* ratio,
                                  float* term, float* rollout_obj, float* group_obj,
                                  uint8_t* skipped, float* J, hipStream_t stream) {
-  if (n_groups > 0)
-    hipLaunchKernelGGL(grpo_group_kernel, dim3((unsigned)n_groups), dim3(kGrpoThreads), 0,
-                       stream, G, n, rewards, offsets, lp_new, lp_old, eps, adv, ratio, term,
-                       rollout_obj, group_obj, skipped);
+#define FORK_GROUPS(WAVES)                                                                     \
+  hipLaunchKernelGGL(grpo_group_kernel<WAVES>, dim3((unsigned)n_groups), dim3(64 * WAVES), 0, \
+                     stream, G, n, rewards, offsets, lp_new, lp_old, eps, adv, ratio, term,    \
+                     rollout_obj, group_obj, skipped)
+  // Sixteen waves pay while the groups run at once (two such workgroups per CU,
+  // 512 in all) and have rollouts for more than four: 16 groups x 16 rollouts x
+  // 15 entries 6.2 -> 4.9 us, 64 x 64 x 100 21 -> 10.  Past that the idle waves
+  // and the larger reductions cost more (4096 x 16 x 15: 25.5 -> 44.8 us), with
+  // 128 rollouts or more from about 2048 groups on (x 300 x 15: 1024 groups 1.4
+  // times as fast as four waves, 4096 0.97 times).
+  if (n_groups > 0) {
+    if (G > 4 && n_groups <= (G >= 128 ? 2048 : 512))
+      FORK_GROUPS(16);
+    else
+      FORK_GROUPS(4);
+  }
+#undef FORK_GROUPS
   hipLaunchKernelGGL(grpo_batch_kernel, dim3(1), dim3(kBatchThreads), 0, stream, n_groups,
                      group_obj, skipped, J);
   return hipGetLastError();

@@ -149,6 +149,49 @@ def _compare_objective(g, ref):
     assert g["J"] == pytest.approx(ref["J"], abs=OBJ_TOL, rel=OBJ_TOL)
 
 
+# either side of the sizes at which a group's workgroup has four or sixteen waves
+@pytest.mark.parametrize("n_groups,G", [(3, 4), (3, 5), (512, 5), (513, 5), (520, 127), (520, 128),
+                                        (2048, 130), (2049, 130)])
+def test_objective_on_both_workgroup_sizes(n_groups, G):
+    _need_gpu()
+    rng = np.random.default_rng(n_groups + G)
+    R = n_groups * G
+    rewards = rng.integers(0, 2, R).astype(np.float32)
+    rewards[:G] = 1
+    offsets = np.concatenate([[0], np.cumsum(rng.integers(0, 3, R))]).astype(np.int32)
+    old = (-3 * rng.random(offsets[-1])).astype(np.float32)
+    new = (old + 0.2 * rng.standard_normal(old.size)).astype(np.float32)
+    g = _objective(rewards, offsets, new, old, G, 0.2)
+    ref = oracle.grpo_objective(rewards.astype(np.float64), offsets, new.astype(np.float64),
+                                old.astype(np.float64), G, float(np.float32(0.2)))
+    _compare_objective(g, ref)
+
+
+def test_more_groups_than_a_launch_of_sixteen_waves_each_holds():
+    """2^22 groups: with 1024 threads each a launch of 2^32 work-items, which is
+    refused."""
+    _need_gpu()
+    ng = (1 << 22) + 3
+    rewards = torch.zeros(ng, 2, device=DEV)
+    rewards[:, 1] = 1
+    rewards[::3] = 1                                       # skipped
+    R = 2 * ng
+    old = torch.zeros(ng, 2, device=DEV)
+    new = torch.zeros(ng, 2, device=DEV)
+    new[:, 1] = math.log(1.1)
+    gobj = torch.full((ng,), -9.0, device=DEV)
+    skip = torch.full((ng,), 9, dtype=torch.uint8, device=DEV)
+    J = torch.zeros(1, device=DEV)
+    _binding.grpo_objective(rewards.view(-1), torch.arange(R + 1, dtype=torch.int32, device=DEV),
+                            new.view(-1), old.view(-1), 2, 0.2, gobj, skip, J)
+    torch.cuda.synchronize()
+    want = torch.full((ng,), 0.05, device=DEV)             # (1.1 - 1) / 2
+    want[::3] = 0
+    assert bool((skip == (torch.arange(ng, device=DEV) % 3 == 0)).all())
+    assert float((gobj - want).abs().max()) < 1e-6
+    assert abs(float(J) - 0.05) < 1e-4                     # binary32 sum of 2.8 million
+
+
 @pytest.mark.parametrize("G", [1, 2, 3, 9, 64, 65, 100, 257, 512, 1000, 1024])
 def test_groups_of_equal_rewards_are_skipped(G):
     """std 0 whatever the rounding of the rewards' sum; a group in which one
