@@ -152,10 +152,9 @@ __global__ __launch_bounds__(kBatchThreads) void grpo_batch_kernel(
 // and nothing is ordered before it: it is selected whenever k > 0, and does
 // not count towards k.
 // Counting a trial is one compare and one bit count per 64 positions, 32
-// trials at most, where comparing every position with every other (the
-// previous kernel) took Lg per position: 256 rollouts x 256 positions 8.8 ->
-// 3.9 us, 342 x 495 30 -> 6.3 us, 66 x 1387 210 -> 7.6 us, 64 x 16384 25.9 ms
-// -> 22 us.
+// trials at most, where comparing every position with every other took Lg per
+// position: 256 rollouts x 256 positions 8.8 -> 3.9 us, 342 x 495 30 -> 6.3 us,
+// 66 x 1387 210 -> 7.6 us, 64 x 16384 25.9 ms -> 22 us.
 template <int kWaves, int N>
 __global__ __launch_bounds__(64 * kWaves) void top_entropy_kernel(
     int Lg, int k, const float* __restrict__ entropy, uint8_t* __restrict__ sel) {
@@ -259,21 +258,32 @@ static_assert(kMaxTopEntropyLen == 64 * 16 * 16, "the largest selection workgrou
 
 hipError_t launch_top_entropy(int R, int Lg, int k, const float* entropy, uint8_t* sel,
                               hipStream_t stream) {
-  if (R == 0) return hipSuccess;
-#define FORK_TOP(WAVES, N)                                                              \
-  hipLaunchKernelGGL((top_entropy_kernel<WAVES, N>), dim3((unsigned)R), dim3(64 * WAVES), \
-                     0, stream, Lg, k, entropy, sel)
+  // a launch holds fewer than 2^32 work-items: more rollouts go in further ones
+#define FORK_TOP(WAVES, N)                                                                    \
+  for (int r0 = 0; r0 < R;) {                                                                 \
+    const int most = (int)(((1LL << 32) - 1) / (64 * WAVES));                                 \
+    const int n = R - r0 < most ? R - r0 : most;                                              \
+    hipLaunchKernelGGL((top_entropy_kernel<WAVES, N>), dim3((unsigned)n), dim3(64 * WAVES),   \
+                       0, stream, Lg, k, entropy + (size_t)r0 * Lg, sel + (size_t)r0 * Lg);   \
+    const hipError_t e = hipGetLastError();                                                   \
+    if (e != hipSuccess) return e;                                                            \
+    r0 += n;                                                                                  \
+  }
   // one wave while a lane holds at most 8 keys (no barrier per trial)
-  if (Lg <= 256)
-    FORK_TOP(1, 4);
+  if (Lg <= 64)
+    FORK_TOP(1, 1)
+  else if (Lg <= 128)
+    FORK_TOP(1, 2)
+  else if (Lg <= 256)
+    FORK_TOP(1, 4)
   else if (Lg <= 512)
-    FORK_TOP(1, 8);
+    FORK_TOP(1, 8)
   else if (Lg <= 2048)
-    FORK_TOP(4, 8);
+    FORK_TOP(4, 8)
   else
-    FORK_TOP(16, 16);
+    FORK_TOP(16, 16)
 #undef FORK_TOP
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 }  // namespace fork

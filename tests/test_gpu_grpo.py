@@ -192,6 +192,25 @@ def test_more_groups_than_a_launch_of_sixteen_waves_each_holds():
     assert abs(float(J) - 0.05) < 1e-4                     # binary32 sum of 2.8 million
 
 
+def test_more_rollouts_than_a_launch_of_sixteen_waves_each_holds():
+    """JustGRPO-Fast on 2^22 rollouts of more than 2048 positions."""
+    _need_gpu()
+    R, Lg = (1 << 22) + 3, 2049
+    if torch.cuda.mem_get_info(DEV)[0] < 80 << 30:
+        pytest.skip("needs 80 GB")
+    gen = torch.Generator(device=DEV).manual_seed(4)
+    ent = torch.empty(R, Lg, device=DEV).uniform_(generator=gen)
+    sel = torch.full((R, Lg), 9, dtype=torch.uint8, device=DEV)
+    _binding.top_entropy(ent, 1, sel)
+    torch.cuda.synchronize()
+    for r in (slice(0, 8), slice(R - 16, R)):
+        want = torch.zeros_like(sel[r])
+        want.scatter_(1, ent[r].argmax(1, keepdim=True), 1)
+        assert torch.equal(sel[r], want)
+    for r0 in range(0, R, 1 << 18):
+        assert bool((sel[r0:r0 + (1 << 18)].sum(1) == 1).all())
+
+
 @pytest.mark.parametrize("G", [1, 2, 3, 9, 64, 65, 100, 257, 512, 1000, 1024])
 def test_groups_of_equal_rewards_are_skipped(G):
     """std 0 whatever the rounding of the rewards' sum; a group in which one
@@ -265,7 +284,7 @@ def test_top_entropy_matches_oracle(R, Lg, k):
     assert np.all(got.sum(axis=1) == k)
 
 
-@pytest.mark.parametrize("Lg", [1, 63, 65, 256, 257, 512, 513, 2048, 2049, 5000])
+@pytest.mark.parametrize("Lg", [1, 63, 64, 65, 128, 129, 256, 257, 512, 513, 2048, 2049, 5000])
 def test_top_entropy_values_and_sizes(Lg):
     """Edges of the positions a lane and a wave hold; infinities, both zeros
     (equal), negative values and NaN: a NaN is ordered before nothing and
