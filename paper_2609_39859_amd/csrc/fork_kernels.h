@@ -95,9 +95,12 @@ hipError_t launch_active_rows(int B, int L, int block_len, const uint8_t* mask,
 // entropy is read by the highest-entropy rule, uniform by the random rule.
 // Row-major state (element k of sequence b at b * L + k): batches of at
 // least kGroupSelectMinB sequences with blocks of at most kGroupSelectMaxBL
-// positions run a group of lanes per sequence (eight from kGroupEightMinB
-// sequences on, four below), others one wave per sequence (as fast up to 4096
-// sequences: 6.3 us, the launch's latency).
+// positions run one to eight lanes per sequence by the block's length, others
+// one wave per sequence (as fast up to 4096 sequences: 6.3 us, the launch's
+// latency).  Blocks of 17 to 32 take eight lanes instead of four from
+// kGroupEightMinB sequences on where rows are off the 16-byte grid (2^19 x rows
+// of 101: 91 -> 80 us), and from four times as many on where they are on it
+// (2^20 x rows of 32: 108 -> 100 us; 2^19: 38.6 against 41).
 // Position-major state (at k * B + b): one lane per four sequences from
 // kPmWideMinB sequences on (B a multiple of 4, the arrays 16-byte aligned),
 // one lane per sequence otherwise.  All give the same results.

@@ -522,6 +522,29 @@ __device__ __forceinline__ int group_xor(int v) {
   return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xf, 0xf, true);
 }
 
+// A value combined over the G = 1, 2, 4 or 8 lanes of a group.
+template <int G, class F>
+__device__ __forceinline__ uint32_t group_all(uint32_t v, F&& f) {
+  if (G >= 2) v = f(v, (uint32_t)group_xor<1>((int)v));
+  if (G >= 4) v = f(v, (uint32_t)group_xor<2>((int)v));
+  if (G == 8) v = f(v, (uint32_t)group_xor<4>((int)v));
+  return v;
+}
+template <int G>
+__device__ __forceinline__ uint32_t group_or(uint32_t v) {
+  return group_all<G>(v, [](uint32_t a, uint32_t b) { return a | b; });
+}
+template <int G>
+__device__ __forceinline__ uint64_t group_or(uint64_t v) {
+  return (uint64_t)group_or<G>((uint32_t)(v >> 32)) << 32 | group_or<G>((uint32_t)v);
+}
+template <int G>
+__device__ __forceinline__ float group_max(float v) {
+  return __uint_as_float(group_all<G>(__float_as_uint(v), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+  }));
+}
+
 // Lowest set bit and bit count of a block's mask.
 __device__ __forceinline__ int low_bit(uint32_t m) { return __ffs((int)m) - 1; }
 __device__ __forceinline__ int low_bit(uint64_t m) { return __ffsll((long long)m) - 1; }
@@ -529,188 +552,199 @@ __device__ __forceinline__ int bit_count(uint32_t m) { return (int)__popc(m); }
 __device__ __forceinline__ int bit_count(uint64_t m) { return (int)__popcll(m); }
 
 // The same rule with G lanes per sequence, for large batches of blocks of at
-// most 32 Q positions (Q = 1, 2), 32 Q / G positions per lane: a wave's loads
-// cover the whole cache lines of 64 / G sequences' blocks, where one lane per
-// sequence (the kernel before) touched 64 lines with each load.  What remains
-// are the commits: a candidate read, a token and a mask byte written, each in
-// a line of its own.
-// One lane per sequence -> G = 4 / G = 8, us, the launch's 6 us of latency
-// included: 4096 sequences x blocks of 32 7.2 -> 6.4 / 6.2, 2^17 14.8 -> 15.0 /
-// 15.6, 2^20 116 -> 97 / 89; 2^17 with the highest-entropy rule or rows off the
-// 16-byte grid 40 -> 20 / 18; 2^17 x blocks of 64 127 -> 24 / 23.  Hence four
-// lanes below kGroupEightMinB sequences, eight above and for blocks over 32.
-// Lane t of a group holds the positions 4 G q + 4 t + {0..3} of the block if its
-// 32 Q entries lie in the row and are aligned for that, else 4 G q + t + {0, G,
-// 2 G, 3 G}.
-template <int Q, int G>
-__global__ __launch_bounds__(256) void select_group_kernel(
-    int B, int L, int BL, float tau, int rule, const float* __restrict__ conf,
+// most P positions, P / G positions per lane: a wave's loads cover the whole
+// cache lines of 64 / G sequences' blocks.  What remains are the commits: a
+// candidate read, a token and a mask byte written, each in a line of its own.
+// P is the least of 4, 8, 16, 32, 64 that holds the block, G chosen so that a
+// lane has four to eight positions.  What more lanes per sequence cost is the
+// work each repeats, with shorter blocks and where one lane reads whole aligned
+// lines most of all.  Measured (us, the mask restored by a copy before each
+// call, together with it): one lane per sequence position by position or, for
+// aligned blocks of at most 32, with wide loads / 32 or 64 positions by four or
+// eight lanes whatever the block / now.  2^20 sequences x blocks of 1: 12.5 / 58 /
+// 11; of 4 33 / 62 / 19; 131072 x 8 17 / 15 / 11; x 32, rows of 32 14.2 / 16.5 /
+// 12.0; rows of 101 78 / 23 / 20; 131072 x 64 130 / 24 / 25; highest entropy,
+// 131072 x 32 68 / 16 / 14.  Slower than one lane: leftmost or random picks of
+// 131072 sequences in rows of 96, 16.0 against 17.2.
+// Lane t of a group holds positions 4 G q + 4 t + {0..3} of the block, in bits of
+// the same numbers.
+template <int P, int G, bool kEnt>
+__global__ __launch_bounds__(1024) void select_group_kernel(
+    int seqs, int B, int L, int BL, float tau, int rule, const float* __restrict__ conf,
     const float* __restrict__ entropy, const float* __restrict__ uniform,
     const int32_t* __restrict__ argmax, int32_t* __restrict__ tokens,
     uint8_t* __restrict__ mask, int32_t* __restrict__ block_start,
     int32_t* __restrict__ fallback, int32_t* __restrict__ ncommit,
     int32_t* __restrict__ commit_pos) {
-  typedef typename std::conditional<Q == 1, uint32_t, uint64_t>::type Bits;
-  constexpr int N = 8 * Q / G;  // quads of positions per lane
-  const int b = blockIdx.x * (256 / G) + threadIdx.x / G;
+  typedef typename std::conditional<P <= 32, uint32_t, uint64_t>::type Bits;
+  constexpr int N = P / (4 * G);  // quads of positions per lane
+  static_assert(N >= 1 && P <= 64, "at least four positions per lane");
+  const int b = blockIdx.x * seqs + threadIdx.x / G;  // seqs: per workgroup
   const int t = threadIdx.x & (G - 1);
   if (b >= B) return;
   const size_t base = (size_t)b * L;
   int32_t* my_commits = commit_pos ? commit_pos + (size_t)b * BL : nullptr;
   const int s = block_start[b];
-  const float* key = rule == kMaxEnt ? entropy : conf;
-  uint32_t mw[Q] = {}, pw[Q] = {};
-  float kv[4 * N];
-  bool wide = false;
-  // the lane's j-th position of its quad q within the block; word 4 G q / 32
-  auto pos = [&](int q, int j) { return 4 * G * q + (wide ? 4 * t + j : t + G * j); };
-  if (s >= 0 && s < L) {
+  const bool inside = s >= 0 && s < L;
+  const size_t first = base + (inside ? s : 0);
+  const bool extreme = kEnt || rule == kMaxConf || rule == kMinConf;
+  float kv[4 * N] = {};  // keys: entropies (kEnt) or confidences
+  Bits mbits = 0, pbits = 0;  // masked positions of the block; those above tau
+  if (inside) {
     const int cnt = min(BL, L - s);
-    const uint8_t* mb = mask + base + s;
-    const float *cb = conf + base + s, *kb = key + base + s;
-    wide = s + 32 * Q <= L &&
-           ((reinterpret_cast<uintptr_t>(cb) | reinterpret_cast<uintptr_t>(kb)) & 15) == 0 &&
-           (reinterpret_cast<uintptr_t>(mb) & 3) == 0;
-    uint32_t m4[N] = {};  // mask bytes of the lane's positions
-    float c[4 * N];
+    const uint8_t* mb = mask + first;
+    const float *cb = conf + first, *kb = kEnt ? entropy + first : cb;
+    const bool wide =
+        s + P <= L &&
+        ((reinterpret_cast<uintptr_t>(cb) | reinterpret_cast<uintptr_t>(kb)) & 15) == 0 &&
+        (reinterpret_cast<uintptr_t>(mb) & 3) == 0;
+    // Every load is unconditional, so that all are in flight together: those
+    // past the block's last position re-read it (or its quad) and are ignored.
+    uint32_t m4[N];  // mask bytes of the lane's positions
+    float c[4 * N] = {};
+    if (wide) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        const unsigned p = min(4 * G * q + 4 * t, (cnt - 1) & ~3);
+        m4[q] = *reinterpret_cast<const uint32_t*>(mb + p);
+        const float4 v = *reinterpret_cast<const float4*>(cb + p);
+        c[4 * q] = v.x, c[4 * q + 1] = v.y, c[4 * q + 2] = v.z, c[4 * q + 3] = v.w;
+      }
+      if (kEnt) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+          const unsigned p = min(4 * G * q + 4 * t, (cnt - 1) & ~3);
+          const float4 u = *reinterpret_cast<const float4*>(kb + p);
+          kv[4 * q] = u.x, kv[4 * q + 1] = u.y, kv[4 * q + 2] = u.z, kv[4 * q + 3] = u.w;
+        }
+      }
+    } else {
+      uint8_t m1[4 * N] = {};
+#pragma unroll
+      for (int i = 0; i < 4 * N; ++i) {
+        if (G == 1 && i >= BL) break;
+        const unsigned p = min(4 * G * (i / 4) + 4 * t + (i & 3), cnt - 1);
+        m1[i] = mb[p];
+        c[i] = cb[p];
+        if (kEnt) kv[i] = kb[p];
+      }
+#pragma unroll
+      for (int q = 0; q < N; ++q)
+        m4[q] = m1[4 * q] | (uint32_t)m1[4 * q + 1] << 8 | (uint32_t)m1[4 * q + 2] << 16 |
+                (uint32_t)m1[4 * q + 3] << 24;
+    }
 #pragma unroll
     for (int q = 0; q < N; ++q) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) c[4 * q + j] = kv[4 * q + j] = 0.f;
-      if (wide) {
-        const int p = 4 * G * q + 4 * t;
-        if (p < cnt) {
-          m4[q] = *reinterpret_cast<const uint32_t*>(mb + p);
-          const float4 v = *reinterpret_cast<const float4*>(cb + p);
-          c[4 * q] = v.x, c[4 * q + 1] = v.y, c[4 * q + 2] = v.z, c[4 * q + 3] = v.w;
-          if (rule == kMaxEnt) {
-            const float4 u = *reinterpret_cast<const float4*>(kb + p);
-            kv[4 * q] = u.x, kv[4 * q + 1] = u.y, kv[4 * q + 2] = u.z, kv[4 * q + 3] = u.w;
-          }
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int p = 4 * G * q + t + G * j;
-          if (p < cnt) {
-            m4[q] |= (uint32_t)mb[p] << (8 * j);
-            c[4 * q + j] = cb[p];
-            if (rule == kMaxEnt) kv[4 * q + j] = kb[p];
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < N; ++q)
+      uint32_t m = 0, above = 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int p = pos(q, j);
-        const bool m = p < cnt && ((m4[q] >> (8 * j)) & 0xffu) != 0;
-        mw[G * q / 8] |= (uint32_t)m << (p & 31);
-        pw[G * q / 8] |= (uint32_t)(m && c[4 * q + j] > tau) << (p & 31);
-        if (rule != kMaxEnt) kv[4 * q + j] = c[4 * q + j];
+        m |= ((m4[q] >> (8 * j)) & 0xffu) != 0 ? 1u << j : 0u;
+        above |= c[4 * q + j] > tau ? 1u << j : 0u;
+        if (!kEnt) kv[4 * q + j] = c[4 * q + j];
       }
-  }
-  // the block's masks: the same for its eight lanes
-  Bits mbits = 0, pbits = 0;
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    mw[q] |= (uint32_t)group_xor<1>((int)mw[q]);
-    pw[q] |= (uint32_t)group_xor<1>((int)pw[q]);
-    mw[q] |= (uint32_t)group_xor<2>((int)mw[q]);
-    pw[q] |= (uint32_t)group_xor<2>((int)pw[q]);
-    if (G == 8) {
-      mw[q] |= (uint32_t)group_xor<4>((int)mw[q]);
-      pw[q] |= (uint32_t)group_xor<4>((int)pw[q]);
+      mbits |= (Bits)m << (4 * G * q + 4 * t);
+      pbits |= (Bits)above << (4 * G * q + 4 * t);
     }
-    mbits |= (Bits)mw[q] << (32 * q);
-    pbits |= (Bits)pw[q] << (32 * q);
+    mbits &= ~(Bits)0 >> (8 * sizeof(Bits) - cnt);  // 1 <= cnt <= P
+    pbits &= mbits;
   }
-  // the extreme key of the masked positions, lowest position on ties.  A scan
-  // in order keeps a NaN at the first masked position and takes no other: the
-  // first counts as the extreme value, the others are left out, so that the
-  // lanes compare ordered keys only and all end with the same position.
-  float best = 0.f;
-  int bi = 0x7fffffff;
-  if (rule == kMaxConf || rule == kMinConf || rule == kMaxEnt) {
-    const bool lowest = rule == kMinConf;
-    const int first = low_bit(mbits);
-#pragma unroll
-    for (int q = 0; q < N; ++q)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float v = kv[4 * q + j];
-        const bool nan = v != v;
-        const float k = nan ? (lowest ? -INFINITY : INFINITY) : v;
-        const bool m = ((mbits >> pos(q, j)) & 1u) && (!nan || pos(q, j) == first);
-        const bool take = m & ((bi == 0x7fffffff) | (lowest ? k < best : k > best));
-        best = take ? k : best;
-        bi = take ? pos(q, j) : bi;
-      }
-    auto combine = [&](float ob, int oi) {
-      const bool better = lowest ? ob < best : ob > best;
-      const bool take =
-          oi != 0x7fffffff && (bi == 0x7fffffff || better || (ob == best && oi < bi));
-      best = take ? ob : best;
-      bi = take ? oi : bi;
-    };
-    combine(__int_as_float(group_xor<1>(__float_as_int(best))), group_xor<1>(bi));
-    combine(__int_as_float(group_xor<2>(__float_as_int(best))), group_xor<2>(bi));
-    if (G == 8) combine(__int_as_float(group_xor<4>(__float_as_int(best))), group_xor<4>(bi));
-  }
+  const Bits mine = mbits;
+  mbits = group_or<G>(mbits);
+  pbits = group_or<G>(pbits);
   if (mbits == 0) {  // no block at s, or nothing masked in it: skip forward
     if (t == 0)
-      lane_rule(b, s >= 0 && s < L ? min(s + BL, L) : s, L, BL, tau, rule, conf, entropy, uniform,
-                argmax, tokens, mask, block_start, fallback, ncommit, my_commits, RowMajor{L});
+      lane_rule(b, inside ? min(s + BL, L) : s, L, BL, tau, rule, conf, entropy, uniform, argmax,
+                tokens, mask, block_start, fallback, ncommit, my_commits, RowMajor{L});
     return;
   }
   const bool fb = pbits == 0;
   Bits commit = pbits;
-  if (fb) {
-    int pick = bi;
-    if (rule == kLeftmost) {
-      pick = low_bit(mbits);
-    } else if (rule == kRandom) {
+  if (fb && extreme) {  // the lanes of a group agree on fb
+    // The extreme key of the masked positions, lowest position on ties.  A
+    // scan in order keeps a NaN at the first masked position and takes no
+    // other: the maximum takes none, and one at the first masked position is
+    // looked for by itself.
+    float best = -INFINITY;
+    uint32_t nan = 0;
+#pragma unroll
+    for (int i = 0; i < 4 * N; ++i) {
+      kv[i] = !kEnt && rule == kMinConf ? -kv[i] : kv[i];
+      const bool m = (mine >> (4 * G * (i / 4) + 4 * t + (i & 3))) & 1u;
+      best = m && kv[i] > best ? kv[i] : best;
+      nan |= kv[i] != kv[i];
+    }
+    best = group_max<G>(best);
+    Bits equal = 0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      uint32_t e = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) e |= kv[4 * q + j] == best ? 1u << j : 0u;
+      equal |= (Bits)e << (4 * G * q + 4 * t);
+    }
+    equal = group_or<G>((Bits)(equal & mine));
+    if (__ballot(nan)) {
+      Bits unordered = 0;
+#pragma unroll
+      for (int i = 0; i < 4 * N; ++i)
+        unordered |= (Bits)(kv[i] != kv[i] ? 1u : 0u) << (4 * G * (i / 4) + 4 * t + (i & 3));
+      unordered = group_or<G>((Bits)(unordered & mine));
+      const Bits lowest = mbits & (~mbits + 1);
+      if (unordered & lowest) equal = lowest;
+    }
+    commit = equal & (~equal + 1);
+  } else if (fb) {
+    int pick = low_bit(mbits);
+    if (rule == kRandom) {
       const int n = bit_count(mbits);
       int j = (int)(uniform[b] * (float)n);
       j = j > n - 1 ? n - 1 : (j < 0 ? 0 : j);
+      // the j-th set bit: the lower half's count decides which half holds it
       Bits rest = mbits;
-      for (int i = 0; i < j; ++i) rest &= rest - 1;  // drop the j lowest
-      pick = low_bit(rest);
+      pick = 0;
+#pragma unroll
+      for (int h = P / 2; h > 0; h /= 2) {
+        const int low = bit_count((Bits)(rest & (((Bits)1 << h) - 1)));
+        const bool up = j >= low;
+        j -= up ? low : 0;
+        rest = up ? rest >> h : rest;
+        pick += up ? h : 0;
+      }
     }
     commit = (Bits)1 << pick;
   }
-  // the candidates all in flight before the first is stored
-  int32_t cand[4 * N];
-#pragma unroll
-  for (int q = 0; q < N; ++q)
+  const int written = bit_count(commit);
+  auto commit_at = [&](int p, int32_t candidate) {
+    mask[first + p] = 0;
+    if (my_commits) my_commits[bit_count((Bits)(commit & (((Bits)1 << p) - 1)))] = s + p;
+    tokens[first + p] = candidate;
+  };
+  if (N == 1) {  // the candidates all in flight before the first is stored
+    const uint32_t own = (uint32_t)(commit >> (4 * t));
+    int32_t cand[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if ((commit >> pos(q, j)) & 1u) cand[4 * q + j] = argmax[base + s + pos(q, j)];
+      if ((own >> j) & 1u) cand[j] = argmax[first + 4 * t + j];
 #pragma unroll
-  for (int q = 0; q < N; ++q)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int p = pos(q, j);
-      if ((commit >> p) & 1u) {
-        mask[base + s + p] = 0;
-        if (my_commits) my_commits[bit_count((Bits)(commit & (((Bits)1 << p) - 1)))] = s + p;
-      }
+    for (int j = 0; j < 4; ++j)
+      if ((own >> j) & 1u) commit_at(4 * t + j, cand[j]);
+  } else {  // the lane's commits in increasing position
+    for (Bits rest = commit & mine; rest; rest &= rest - 1) {
+      const int p = low_bit(rest);
+      commit_at(p, argmax[first + p]);
     }
-  const int written = bit_count(commit);
+  }
   if (my_commits)
     for (int i = t; i < BL; i += G)
       if (i >= written) my_commits[i] = -1;
-  if (t == 0) {
+  // block_start[b] stays s.  Lane 0 stores the flag and lane 1 the count, with
+  // one instruction.
+  if (G >= 2 && ncommit) {
+    if (t < 2) (t == 0 ? fallback : ncommit)[b] = t == 0 ? (fb ? 1 : 0) : written;
+  } else if (t == 0) {
     fallback[b] = fb ? 1 : 0;
-    block_start[b] = s;
     if (ncommit) ncommit[b] = written;
   }
-#pragma unroll
-  for (int q = 0; q < N; ++q)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if ((commit >> pos(q, j)) & 1u) tokens[base + s + pos(q, j)] = cand[4 * q + j];
 }
 
 // Position-major state (element (b, k) at k * B + b): one lane per group of
@@ -1011,14 +1045,35 @@ hipError_t launch_select(int B, int L, int block_len, float tau, int rule,
 #undef FORK_SELECT_PM
   }
   else if (B >= kGroupSelectMinB && block_len <= kGroupSelectMaxBL) {
-#define FORK_SELECT_GROUP(Q, G)                                                                  \
-  hipLaunchKernelGGL((select_group_kernel<Q, G>), dim3((unsigned)((B + 256 / G - 1) / (256 / G))), \
-                     dim3(256), 0, stream, B, L, block_len, tau, rule, conf, entropy, uniform,   \
+    // 256 / G sequences per workgroup; with blocks of 17 to 32 and a large batch
+    // 8 KiB of mask instead, the share that an elementwise kernel gives its
+    // workgroups: a mask just written by one is then found in the L2 of the
+    // same XCD (131072 sequences, rows of 32: 13.3 -> 11.8 us with 256 sequences;
+    // rows of 64: 15.9 -> 14.0 with 128).
+    auto seqs = [&](int g) {
+      if (g != 4 || B < 16384) return 256 / g;
+      return L <= 32 ? 256 : L <= 64 ? 128 : 64;
+    };
+#define FORK_SELECT_KEYS(P, G, ENT)                                                              \
+  hipLaunchKernelGGL((select_group_kernel<P, G, ENT>),                                          \
+                     dim3((unsigned)(((long long)B + seqs(G) - 1) / seqs(G))), dim3(G * seqs(G)), \
+                     0, stream, seqs(G), B, L, block_len, tau, rule, conf, entropy, uniform,     \
                      argmax, tokens, mask, block_start, fallback, ncommit, commit_pos)
-    if (block_len > 32) FORK_SELECT_GROUP(2, 8);
-    else if (B < kGroupEightMinB) FORK_SELECT_GROUP(1, 4);
-    else FORK_SELECT_GROUP(1, 8);
+#define FORK_SELECT_GROUP(P, G)               \
+  do {                                        \
+    if (rule == kMaxEnt)                      \
+      FORK_SELECT_KEYS(P, G, true);           \
+    else                                      \
+      FORK_SELECT_KEYS(P, G, false);          \
+  } while (0)
+    if (block_len <= 4) FORK_SELECT_GROUP(4, 1);
+    else if (block_len <= 8) FORK_SELECT_GROUP(8, 2);
+    else if (block_len <= 16) FORK_SELECT_GROUP(16, 2);
+    else if (block_len > 32) FORK_SELECT_GROUP(64, 8);
+    else if (B >= (L % 4 ? kGroupEightMinB : 4 * kGroupEightMinB)) FORK_SELECT_GROUP(32, 8);
+    else FORK_SELECT_GROUP(32, 4);
 #undef FORK_SELECT_GROUP
+#undef FORK_SELECT_KEYS
   }
   else
     hipLaunchKernelGGL(select_kernel, dim3((unsigned)B), dim3(64), 0, stream, L,

@@ -1,8 +1,8 @@
 """GPU parity of the unmasking rule on its own (fork_select, Algorithm 2 and
-the fallback rules of Algorithm 1 and Section 4.1): both kernel paths (one
-wave per sequence, and one lane per sequence for large batches of short
-blocks) against the oracle, bit for bit (both sides decide on the same
-binary32 confidences)."""
+the fallback rules of Algorithm 1 and Section 4.1): its kernels (one wave per
+sequence, one to eight lanes per sequence for large batches of short blocks,
+and the position-major ones) against the oracle, bit for bit (both sides decide
+on the same binary32 confidences)."""
 import numpy as np
 import pytest
 import torch
@@ -70,10 +70,10 @@ def _run(conf, ent, am, tok, msk, bs, uni, B, L, BL, tau, rule,
 
 
 SHAPES = [
-    # B, L, block_len   (B >= 4096 with block_len <= 64 takes the lane path)
+    # B, L, block_len   (B >= 4096 with block_len <= 64: a group of lanes each)
     (5, 61, 7), (37, 300, 300), (4096, 40, 8), (5000, 64, 64), (4100, 33, 32),
     (4096, 100, 65), (4097, 1, 1),
-    # lane path with 16-byte aligned rows and blocks <= 32 (wide loads)
+    # lane groups with 16-byte aligned rows (wide loads)
     (4096, 32, 32), (4096, 64, 16), (8192, 96, 32), (4096, 48, 8),
 ]
 
@@ -126,9 +126,8 @@ def _check_against_oracle(B, L, BL, rule, layout, shared_start=False):
 @pytest.mark.parametrize("outputs", ["all", "none"])
 def test_row_major_whole_wave_blocks(B, L, BL, rule, outputs):
     """Row-major batches whose blocks start on multiples of 16 positions
-    with 32 positions left in the row (the lane path's wide loads), every
-    other wave with one sequence off that grid (its position-by-position
-    path) and the last sequence idle, under the threshold, leftmost, random
+    with 32 positions left in the row (wide loads), one sequence in 128 off that
+    grid (loads of single positions) and the last sequence idle, under the threshold, leftmost, random
     and highest-confidence rules, with and without the commit outputs.
     Against the oracle, bit for bit."""
     _need_gpu()
@@ -153,13 +152,46 @@ def test_row_major_whole_wave_blocks(B, L, BL, rule, outputs):
 
 
 @pytest.mark.parametrize("L,BL", [(32, 32), (33, 31), (64, 32), (67, 33), (72, 40), (64, 64),
-                                  (131, 63), (200, 64), (9, 5)])
+                                  (131, 63), (200, 64), (9, 5), (1, 1), (5, 2), (4, 4), (8, 8),
+                                  (32, 8), (27, 7), (16, 16), (50, 9), (64, 16), (33, 17)])
 @pytest.mark.parametrize("rule", [0, 1, 2, 3, 4])
 def test_lane_groups_match_oracle(L, BL, rule):
-    """Blocks around 32 and 64 positions, rows and starts on and off the
-    16-byte grid, blocks cut by the row's end, and a last workgroup that is
-    not full."""
+    """Blocks around the lengths at which the lanes per sequence change (4, 8,
+    16, 32), rows and starts on and off the 16-byte grid, blocks cut by the
+    row's end, and a last workgroup that is not full."""
     _check_against_oracle(4099, L, BL, rule, _binding.FORK_LAYOUT_ROW_MAJOR)
+
+
+@pytest.mark.parametrize("B,L,BL", [(16389, 32, 32), (16389, 32, 20), (16389, 64, 32), (16389, 99, 31),
+                                    ((1 << 18) + 1, 33, 32), ((1 << 18) + 1, 21, 18),
+                                    ((1 << 20) + 3, 32, 32)])
+@pytest.mark.parametrize("rule", [0, 1, 2, 3, 4])
+def test_large_batches_match_oracle(B, L, BL, rule):
+    """Workgroups of 256, 128 and 64 sequences, and eight lanes per sequence on
+    and off the 16-byte grid."""
+    _need_gpu()
+    _check_whole(_state(B, L, 1000, B + L + BL + rule), B, L, BL, rule, 0.9)
+
+
+def test_more_sequences_than_a_launch_of_eight_lanes_each_holds():
+    """2^29 sequences of one position: with eight lanes each a launch of 2^32
+    work-items, which is refused."""
+    _need_gpu()
+    B = (1 << 29) + 5
+    if torch.cuda.mem_get_info(DEV)[0] < 16 << 30:
+        pytest.skip("needs 16 GB")
+    i32 = dict(dtype=torch.int32, device=DEV)
+    conf = torch.zeros(B, device=DEV)
+    cand = torch.arange(B, **i32)
+    tok, start, fb = torch.full((B,), -1, **i32), torch.zeros(B, **i32), torch.full((B,), -9, **i32)
+    msk = torch.ones(B, dtype=torch.uint8, device=DEV)
+    msk[::3] = 0
+    _binding.select(conf, cand, tok, msk, start, 1, 0.5, fb, B=B, L=1, rule=1)
+    torch.cuda.synchronize()
+    assert not msk.any()
+    assert bool((fb[::3] == -1).all()) and bool((fb[1::3] == 1).all()) and bool((fb[2::3] == 1).all())
+    assert bool((tok[::3] == -1).all())
+    assert torch.equal(tok[1::3], cand[1::3]) and torch.equal(tok[2::3], cand[2::3])
 
 
 def _check_whole(state, B, L, BL, rule, tau, layout=_binding.FORK_LAYOUT_ROW_MAJOR):
@@ -199,10 +231,11 @@ def _nan_state(B, L, BL, rule):
 
 
 @pytest.mark.parametrize("B,L,BL", [(4099, 32, 32), (4099, 67, 31), (4099, 64, 64), (4099, 131, 40),
-                                    ((1 << 18) + 3, 32, 32), ((1 << 18) + 3, 37, 20)])
+                                    ((1 << 18) + 3, 32, 32), ((1 << 18) + 3, 37, 20), (4099, 4, 4),
+                                    (4099, 7, 3), (4099, 16, 8), (4099, 40, 16), (4099, 45, 13)])
 @pytest.mark.parametrize("rule", [1, 2, 3])
 def test_nan_keys_follow_the_scan_in_order(B, L, BL, rule):
-    """Four and eight lanes per sequence, blocks up to 32 and up to 64
+    """One to eight lanes per sequence, blocks up to 4, 8, 16, 32 and 64
     positions: one position is committed, the one a scan in order picks."""
     _need_gpu()
     _check_whole(_nan_state(B, L, BL, rule), B, L, BL, rule, 0.9)
@@ -220,8 +253,8 @@ def test_nan_keys_in_small_batches(B, L, BL, layout, rule):
 
 
 def test_lane_and_wave_paths_agree():
-    """The first sequences of a large batch (lane path) and the same
-    sequences run as a small batch (wave path) give identical results."""
+    """The first sequences of a large batch (a group of lanes each) and the same
+    sequences run as a small batch (a wave each) give identical results."""
     _need_gpu()
     B, L, BL = 4096, 64, 32
     conf, ent, am, tok, msk, bs, uni = _state(B, L, 500, 7)
