@@ -4,11 +4,14 @@
 // What bounds it is the fp32 matrix rate: one MFMA of 2048 flop takes 32
 // cycles, 1/16 of the bf16 rate, so LDS and L2 traffic are secondary and the
 // work goes where it fills the 256 CUs: a workgroup holds 256 vocabulary rows
-// x 16 N positions (N = 1, 2, 4, 8, chosen by choose() from the sizes), eight
+// x 16 N positions (N = 1, 2, 4, chosen by choose() from the sizes), eight
 // waves of 32 rows each, so no matrix work is spent on a padded position tile
 // and a small step still spreads over several CUs.  K is staged through LDS in
-// 128-byte slabs (32 fp32) by buffer loads that write LDS directly, three
-// slots per operand; a wave loads its own W rows.  A 16-byte LDS read gives a
+// 128-byte slabs (32 fp32) by buffer loads that write LDS directly; a wave loads
+// its own W rows.  A tile alone on its CU has three slots per operand, so that its
+// loads run two stages ahead; with more tiles than CUs two slots (at most 80 KiB)
+// let two tiles share a CU, and one's statistics and first loads run under the
+// other's main loop.  A 16-byte LDS read gives a
 // lane four consecutive K values of a row, the operands of four MFMAs (MFMA m
 // sums element m of the four lane groups' chunks).
 //
@@ -16,15 +19,15 @@
 // position are merged in order through LDS.  The sums are the same for every
 // N, so a row's partials have the same bits whichever tile a launch takes.
 #include "lmhead_device.h"
+#include "lmhead_tiles.h"
 
 namespace fork {
 namespace {
 
 constexpr int kWaves = 8;
 constexpr int kWaveRows = 32;
-constexpr int kSlots = 3;
 
-template <int NJ, int kMode>
+template <int NJ, int kSlots, int kMode>
 __device__ __forceinline__ void gemm_f32_body(
     const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ W, int M, int d,
     int V, int nvt, int npt, int pt0, float4* __restrict__ partials,
@@ -128,16 +131,17 @@ __device__ __forceinline__ void gemm_f32_body(
     col_in[j] = kMode != kGreedy && p < M ? src[p] : -1;
   }
 
-  issue(0, 0);
-  issue(1, 1);
-  int slot = 0, slot2 = 2;
+  constexpr int kAhead = kSlots > 1 ? kSlots - 1 : 1;  // stages issued before their turn
+#pragma unroll
+  for (int s = 0; s < kAhead; ++s) issue(s, s);
+  int slot = 0, next = kAhead;
   for (int k = 0; k < nk; ++k) {
-    // stage k resident (stage k + 1 may be in flight), all waves done with
-    // stage k - 1, whose slot takes stage k + 2; stages past the end read as
-    // zero into slots nobody reads
-    wait_vm_lgkm0<LW + LH>();
+    // stage k resident (with three slots stage k + 1 may be in flight), all
+    // waves done with stage k - 1, whose slot takes stage k + kAhead; stages
+    // past the end read as zero into slots nobody reads
+    wait_vm_lgkm0<(kAhead - 1) * (LW + LH)>();
     barrier_nofence();
-    issue(k + 2, slot2);
+    if (kSlots > 1) issue(k + kAhead, next);
     const unsigned char* sw = smem + slot * kOperandBytes + (wave * kWaveRows + fr) * kSlab;
     const unsigned char* sh = smem + kSlots * kOperandBytes + slot * kHBytes + fr * kSlab;
 #pragma unroll
@@ -157,7 +161,7 @@ __device__ __forceinline__ void gemm_f32_body(
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][m], b[j][m], acc[i][j], 0, 0, 0);
     }
     slot = slot == kSlots - 1 ? 0 : slot + 1;
-    slot2 = slot2 == kSlots - 1 ? 0 : slot2 + 1;
+    next = next == kSlots - 1 ? 0 : next + 1;
   }
   // loads into LDS still in flight must neither overwrite the exchange below
   // nor outlive the workgroup
@@ -169,13 +173,21 @@ __device__ __forceinline__ void gemm_f32_body(
   auto stats = [&](auto full_tag) {
     constexpr bool kFull = decltype(full_tag)::value;
     const int vbase = v0 + wave * kWaveRows;
+    float4 st[NJ];  // all columns before the first is stored: their chains overlap
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const int c = Lay::col(j, lane);
       float m, s, t;
       int idx;
       column_stats<Lay, kFull>(acc, j, lane, vbase, V, m, idx, s, t);
-      if (lane < Lay::kLeaders) red[wave * kTP + c] = make_float4(m, s, t, __int_as_float(idx));
+      st[j] = make_float4(m, s, t, __int_as_float(idx));
+    }
+    if (lane < Lay::kLeaders) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) red[wave * kTP + Lay::col(j, lane)] = st[j];
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int c = Lay::col(j, lane);
       if (kMode == kTarget) {
         float z;
         if (column_target<Lay>(acc, j, lane, vbase, V, col_in[j], z)) ta.z[p0 + c] = z;
@@ -209,15 +221,15 @@ __device__ __forceinline__ void gemm_f32_body(
   }
 }
 
-template <int NJ, int kMode>
-__global__ __launch_bounds__(64 * kWaves, 2) void gemm_f32_kernel(
+template <int NJ, int kSlots, int kMode>
+__global__ __launch_bounds__(64 * kWaves, kSlots == 1 ? 6 : kSlots == 2 ? 4 : 2) void gemm_f32_kernel(
     const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ W, int M, int d,
     int V, int nvt, int npt, int pt0, float4* __restrict__ partials,
     const int32_t* __restrict__ rowlist, int Mh, SampleArgs sa, TargetArgs ta) {
-  gemm_f32_body<NJ, kMode>(hidden, W, M, d, V, nvt, npt, pt0, partials, rowlist, Mh, sa, ta);
+  gemm_f32_body<NJ, kSlots, kMode>(hidden, W, M, d, V, nvt, npt, pt0, partials, rowlist, Mh, sa, ta);
 }
 
-template <int NJ>
+template <int NJ, int kSlots>
 hipError_t launch(const void* hidden, const void* W, int M, int d, int V, float4* partials,
                   const int32_t* rowlist, int Mh, const SampleArgs& sample,
                   const TargetArgs& target, hipStream_t stream) {
@@ -232,7 +244,7 @@ hipError_t launch(const void* hidden, const void* W, int M, int d, int V, float4
     const int n = npt - pt0 < most ? npt - pt0 : most;
     const dim3 grid((unsigned)(nvt * n)), block(64 * kWaves);
 #define FORK_LAUNCH(MODE)                                                                      \
-  hipLaunchKernelGGL((gemm_f32_kernel<NJ, MODE>), grid, block, 0, stream, h, w, M, d, V, nvt, \
+  hipLaunchKernelGGL((gemm_f32_kernel<NJ, kSlots, MODE>), grid, block, 0, stream, h, w, M, d, V, nvt, \
                      n, pt0, partials, rowlist, Mh, sample, target)
     if (target.token)
       FORK_LAUNCH(kTarget);
@@ -247,24 +259,32 @@ hipError_t launch(const void* hidden, const void* W, int M, int d, int V, float4
   return hipSuccess;
 }
 
-// 16-position columns per wave.  A tile of 1, 2, 4 or 8 columns takes 1 : 1.43
-// : 2.31 : 4.15 (measured, one round of tiles at d = 1024: 32 / 46 / 74 / 133
-// us), and the 256 CUs take one tile each per round.  Measured with 1, 2, 4, 8
-// columns (us; the register-staged 256-position kernel before: 73 at the first
-// size, 59 TFLOP/s at the last): M = 64, d = 256, V = 1024: 12.9 / 17 / 25 /
-// 41; M = 128, d = 1024, V = 32000: 120 / 94 / 81 / 136; M = 2048, d = 1024,
-// V = 15808: 827 / 666 / 571 / 526 (126 TFLOP/s; a library product of 8192^3
-// reaches 149).
+// 16-position columns per wave: the least time of the launch by the rounds it
+// takes.  More than 256 tiles run two to a CU (the two-slot ring), rounds of 512:
+// a pair of tiles of 1, 2 or 4 columns takes 1.75, 2.25, 3.8 times one tile of one
+// column alone, and tiles alone on their CU (up to 256, the three-slot ring, or the
+// rest of the rounds) 1, 1.3, 2.2.  Over 1106 random sizes (d = 4 .. 8192, M to 10000,
+// V to 126000) the choice is 0.8% slower than the best of the six for each size and
+// 18% at most.  Tiles of 8 columns, one to a CU, were 3 to 20% slower than 4 columns
+// two to a CU wherever several rounds run (M = 4000, V = 41661, us per 256 x 64
+// tile and CU: d = 128 12.1 / 10.6, 256 19.7 / 18.2, 1024 67.6 / 64.2).
+// Rows of one stage (d <= 32) need one slot: three tiles of 4 columns to a CU (4.7
+// -> 4.0 us).  A kernel with 256 positions per workgroup and registers between
+// global memory and LDS was faster only where a tile is little more than its
+// statistics: d <= 32 by up to 8%, d = 40 .. 70 by up to 11% (6.0 to 7.3 us against
+// 6.7 to 7.3), d = 70 .. 110 by up to 6%; larger d by 3% at most, and up to 5 times
+// slower where few tiles run.
 int choose(int M, int V) {
-  constexpr long long kCus = 256;
   const long long nvt = num_vocab_tiles(V);
-  const int cols[4] = {1, 2, 4, 8};
-  const int cost[4] = {100, 143, 231, 415};
+  const int cols[3] = {1, 2, 4};
+  const int alone[3] = {100, 130, 220}, pair[3] = {175, 225, 380};
   int best = 0;
   long long least = 0;
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 3; ++i) {
     const long long tiles = nvt * (((long long)M + 16 * cols[i] - 1) / (16 * cols[i]));
-    const long long c = (tiles + kCus - 1) / kCus * cost[i];
+    const long long rest = tiles % (2 * kCus);
+    const long long c = tiles / (2 * kCus) * pair[i] +
+                        (rest == 0 ? 0 : rest <= kCus ? alone[i] : pair[i]);
     if (i == 0 || c < least) {
       best = i;
       least = c;
@@ -280,12 +300,17 @@ hipError_t launch_gemm_f32(const void* hidden, const void* W, int M, int d, int 
                            const SampleArgs& sample, const TargetArgs& target,
                            hipStream_t stream) {
   const int n = choose(M, V);
-#define FORK_F32(NJ) \
-  launch<NJ>(hidden, W, M, d, V, partials, rowlist, Mh, sample, target, stream)
+  const bool two =
+      num_vocab_tiles(V) * (((long long)M + 16 * n - 1) / (16 * n)) > kCus;  // two to a CU
+#define FORK_F32(NJ)                                                                              \
+  (two ? launch<NJ, 2>(hidden, W, M, d, V, partials, rowlist, Mh, sample, target, stream) \
+       : launch<NJ, 3>(hidden, W, M, d, V, partials, rowlist, Mh, sample, target, stream))
   if (n == 1) return FORK_F32(1);
   if (n == 2) return FORK_F32(2);
-  if (n == 4) return FORK_F32(4);
-  return FORK_F32(8);
+  // rows of one stage: one slot, 40 KiB, three to a CU
+  if (two && d <= kSlab / 4)
+    return launch<4, 1>(hidden, W, M, d, V, partials, rowlist, Mh, sample, target, stream);
+  return FORK_F32(4);
 #undef FORK_F32
 }
 

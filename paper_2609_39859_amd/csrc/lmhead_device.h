@@ -211,7 +211,10 @@ __device__ __forceinline__ void column_stats(typename Lay::Arr& acc, int j, int 
     idx = take ? io : idx;
   });
   float s = 0.f, tl = 0.f;
-  if (m > -INFINITY) {
+  // with few rows per lane the sums are taken without a branch, so that the
+  // columns' chains of exchanges can overlap
+  constexpr bool kBranch = Lay::kNI > 2;
+  if (!kBranch || m > -INFINITY) {
     const float nml = -m * kLog2e;
 #pragma unroll
     for (int i = 0; i < Lay::kNI; ++i)
@@ -233,8 +236,8 @@ __device__ __forceinline__ void column_stats(typename Lay::Arr& acc, int j, int 
   });
   m_out = m;
   idx_out = idx;
-  s_out = s;
-  t_out = tl * kLn2;
+  s_out = kBranch || m > -INFINITY ? s : 0.f;
+  t_out = kBranch || m > -INFINITY ? tl * kLn2 : 0.f;
 }
 
 // The logit of row tk (a given token) in column j, if this lane holds it among

@@ -1,5 +1,5 @@
 """The LM head's position tiles: launches of different sizes take tiles of 64,
-128 or 256 positions (fp32: 16, 32, 64 or 128), and a row's statistics must
+128 or 256 positions (fp32: 16, 32 or 64), and a row's statistics must
 not depend on which."""
 import numpy as np
 import pytest
@@ -73,13 +73,15 @@ def test_drawn_candidates_of_a_ragged_tile(V, M, dtype):
 
 # V = 32000 (125 vocabulary tiles): 1024 rows take tiles of 256 positions, 160
 # rows tiles of 128, 40 rows tiles of 64; V = 2000 takes 64 throughout; fp32
-# tiles of 16, 32, 64 and 128 in turn
+# tiles of 16, 32, 64 alone on a CU and 64 two to a CU, then (274 vocabulary
+# tiles) 16, 32 and 64 two to a CU
 @pytest.mark.parametrize("V,sizes,dtype", [(32000, (40, 160, 1024), torch.bfloat16),
                                            (2000, (3, 70, 300), torch.bfloat16),
-                                           (32000, (16, 48, 128, 256), torch.float32)])
+                                           (32000, (16, 48, 128, 256), torch.float32),
+                                           (70000, (16, 32, 300), torch.float32)])
 @pytest.mark.parametrize("temperature", [0.0, 0.8])
-def test_rows_do_not_depend_on_the_tile(V, sizes, dtype, temperature):
-    d = 72
+@pytest.mark.parametrize("d", [32, 72])  # one stage (fp32: three tiles to a CU), and more
+def test_rows_do_not_depend_on_the_tile(V, sizes, dtype, temperature, d):
     h, W = _inputs(max(sizes), d, V, V, dtype)
     outs = [_step(h[:n].contiguous(), W, temperature) for n in sizes]
     for n, g in zip(sizes[:-1], outs[:-1]):
