@@ -39,9 +39,12 @@ inline int tail_tiles(long long n) {
 // 256 .. 4096, V = 2000 .. 32000, one round of tiles: 9.4 / 12.2 / 16.2 us,
 // 14.3 / 19.9 / 27.5 us, 36.5 / 53 / 73 us; with every CU busy 39 / 58 / 94
 // us), and the 256 CUs take one tile each per round, so the cost of a launch is
-// the rounds times the tile's.  Rows that are not whole cache lines make the
-// smaller tiles, which load more per flop, dearer once more than one round runs
-// (d = 3504, M = 1294, V = 23341: 392 / 257 / 228 us).  Examples (us, 64 / 128
+// the rounds times the tile's.  Rows that are not whole cache lines, and long
+// rows, make the smaller tiles, which load more per flop, dearer once more than
+// one round runs (d = 3504, M = 1294, V = 23341: 392 / 257 / 228 us; d = 3584, M =
+// 142, V = 85185 202 / 172 / 159, M = 266, V = 48270 160 / 134 / 133).  Over 5663
+// random sizes (d = 64 .. 4096, M to 3000, V to 130000) the choice is 0.6% slower
+// than the best tile for each, and nowhere more than 4% slower than 256 positions.  Examples (us, 64 / 128
 // / 256 positions): V = 8000, d = 1024: M = 512 16 / 22 / 28, M = 1024 28 / 23 /
 // 29; V = 32000, d = 1024: M = 128 20 / 24 / 25, M = 256 30 / 27 / 30, M = 1024
 // 98 / 79 / 63.
@@ -49,7 +52,7 @@ inline TileChoice choose_tile(int M, int d, int nvt, bool lines, long long w_byt
   auto tiles = [&](int p) { return ((long long)M + p - 1) / p; };
   auto cost = [&](int p, int per_round) {
     const long long n = nvt * tiles(p);
-    const bool dear = p < 256 && n > kCus && !lines;
+    const bool dear = p < 256 && n > kCus && (!lines || d >= 2560);
     return (n + kCus - 1) / kCus * per_round * (dear ? 12 : 10);
   };
   const long long c64 = cost(64, 100), c128 = cost(128, 145);

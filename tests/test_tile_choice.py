@@ -46,3 +46,11 @@ def test_rows_that_are_not_whole_lines_are_loaded_cached(choose):
 def test_a_large_w_read_once_is_loaded_past_the_caches(choose, M, positions, two):
     c, = choose([(M, 4096, 126464, 0)])
     assert c == dict(narrow=1, positions=positions, nontemporal=1, two_per_cu=two)
+
+
+# several rounds of 64-position tiles over long rows, up to 1.28 times the time
+# of the 256-position kernel
+@pytest.mark.parametrize("M,d,V", [(142, 3584, 85185), (266, 3584, 48270), (315, 3072, 43853),
+                                   (192, 4096, 41054), (957, 4096, 8518)])
+def test_long_rows_in_several_rounds_take_larger_tiles(choose, M, d, V):
+    assert choose([(M, d, V, 0)])[0]["positions"] > 64
