@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -135,16 +136,29 @@ def lib():
         L.fork_select.argtypes = [ctypes.POINTER(ForkSelectArgs)]
         L.fork_top_entropy.restype = ctypes.c_int
         L.fork_top_entropy.argtypes = [_P, _I32, _I32, _I32, _P, _P]
+        _fast = _load_fast(L)
         _lib = L
-        raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw_stream is not None and os.path.exists(os.path.join(_HERE, "_fastcall.so")):
-            from . import _fastcall
-            _fastcall.init(raw_stream, *(
+    return _lib
+
+
+def _load_fast(L):
+    """The native form of the plain calls, or None: every call is then checked
+    and made here, with the same results."""
+    raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw_stream is None or not os.path.exists(os.path.join(_HERE, "_fastcall.so")):
+        return None
+    try:
+        from . import _fastcall
+        _fastcall.init(raw_stream, *(ctypes.sizeof(c) for c in (
+            ForkStepArgs, ForkLogprobArgs, ForkGrpoArgs, ForkSelectArgs)), *(
                 ctypes.cast(f, _P).value for f in (
                     L.fork_step_ex, L.fork_step_noalloc, L.fork_logprob, L.fork_grpo_objective,
                     L.fork_select, L.fork_top_entropy)))
-            _fast = _fastcall
-    return _lib
+    except (ImportError, TypeError) as e:
+        warnings.warn("calls are made through ctypes: _fastcall.so does not fit this "
+                      "interpreter, torch or library (%s)" % e, RuntimeWarning, stacklevel=3)
+        return None
+    return _fastcall
 
 
 def _plain(name, *args) -> bool:

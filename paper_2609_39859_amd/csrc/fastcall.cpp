@@ -315,16 +315,28 @@ PyObject* top_entropy(PyObject*, PyObject* const* v, Py_ssize_t nargs) {
   });
 }
 
-// init(raw_stream, step_ex, step_noalloc, logprob, grpo, select, top_entropy):
-// torch's raw-stream function and the addresses of the library's functions.
+// init(raw_stream, sizes of the four argument structures, step_ex,
+// step_noalloc, logprob, grpo, select, top_entropy): torch's raw-stream
+// function, what the caller takes the structures to be, and the addresses of
+// the library's functions.
 PyObject* init(PyObject*, PyObject* const* v, Py_ssize_t nargs) {
-  if (nargs != 7) {
-    PyErr_SetString(PyExc_TypeError, "init takes 7 arguments");
+  if (nargs != 11) {
+    PyErr_SetString(PyExc_TypeError, "init takes 11 arguments");
     return nullptr;
+  }
+  const size_t sizes[4] = {sizeof(fork_step_args), sizeof(fork_logprob_args),
+                           sizeof(fork_grpo_args), sizeof(fork_select_args)};
+  for (int i = 0; i < 4; ++i) {
+    const size_t n = PyLong_AsSize_t(v[i + 1]);
+    if (PyErr_Occurred()) return nullptr;
+    if (n != sizes[i]) {
+      PyErr_SetString(PyExc_ImportError, "built for other argument structures");
+      return nullptr;
+    }
   }
   void* p[6];
   for (int i = 0; i < 6; ++i) {
-    p[i] = PyLong_AsVoidPtr(v[i + 1]);
+    p[i] = PyLong_AsVoidPtr(v[i + 5]);
     if (!p[i]) {
       if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null function address");
       return nullptr;
