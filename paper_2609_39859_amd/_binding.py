@@ -4,8 +4,9 @@ Argument marshalling only: shapes, dtypes, devices and contiguity are checked,
 then raw device pointers and the current HIP stream are handed to the library,
 where every step of the computation runs in HIP kernels.  Plain calls (torch
 tensors, Python numbers) are checked and made natively (csrc/fastcall.cpp);
-anything else, and whatever fails a check there, goes through the checks here.  There is no CPU or
-PyTorch fallback: if the library is missing the first call raises.
+anything else, whatever fails a check there, and the call that loads the
+library go through the checks here.  There is no CPU or PyTorch fallback: if
+the library is missing the first call raises.
 """
 from __future__ import annotations
 
@@ -163,9 +164,8 @@ def _load_fast(L):
 
 def _plain(name, *args) -> bool:
     """Make the call natively.  False if an argument is not of the plain form
-    or fails a check; the caller then checks and calls by itself."""
-    if _lib is None:
-        lib()
+    or fails a check, or the library is not loaded yet; the caller then checks
+    and calls by itself."""
     if _fast is None:
         return False
     rc = getattr(_fast, name)(*args)

@@ -45,3 +45,20 @@ def test_native_calls_that_do_not_fit_are_left_out(tmp_path, other):
              "    assert [x.category for x in w] == [RuntimeWarning], w\n"
              "assert b._fast is None and b.version() == first\n")
     _run(tmp_path, code)
+
+
+def test_arguments_are_checked_before_the_library_is_loaded(tmp_path):
+    """Without the library a wrong argument is reported as such."""
+    _copy(tmp_path)
+    out = _run(tmp_path, """
+import torch, %s._binding as b
+t = torch.zeros(4, 4)
+for call in (lambda: b.top_entropy(t, 1, t), lambda: b.grpo_objective(t, t, t, t, 2, 0.2, t, t, t),
+             lambda: b.fork_step_ex(t, t, t, t, t, 1, 0.5, t, t, t, t, B=2, L=2),
+             lambda: b.select(t, t, t, t, t, 1, 0.5, t, B=1, L=1), lambda: b.logprob(t, t, t, t)):
+    try:
+        call()
+    except (TypeError, ValueError) as e:
+        print(type(e).__name__, e)
+""" % NAME)
+    assert len(out.splitlines()) == 5 and "GPU" in out
