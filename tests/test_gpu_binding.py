@@ -55,9 +55,23 @@ def _calls():
         out_sel=torch.zeros(3, 70, dtype=torch.uint8, device=DEV)))
 
 
-def _both(monkeypatch, fn, kw, change):
+class _Spy:
+    """_fastcall, keeping what its functions returned."""
+
+    def __init__(self, fast):
+        self.fast, self.returned = fast, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.returned.append(getattr(self.fast, name)(*args))
+            return self.returned[-1]
+        return call
+
+
+def _both(monkeypatch, fn, kw, change, taken=False):
     """(outcome natively, outcome by the binding's own checks) of fn(**kw)
-    with `change` applied to fresh copies of the arguments."""
+    with `change` applied to fresh copies of the arguments; taken: the native
+    function made the call."""
     _binding.lib()
     assert _binding._fast is not None
     out = []
@@ -65,14 +79,15 @@ def _both(monkeypatch, fn, kw, change):
         args = {k: v.clone() if isinstance(v, torch.Tensor) else v for k, v in kw.items()}
         change(args)
         with monkeypatch.context() as m:
-            if not native:
-                m.setattr(_binding, "_fast", None)
+            spy = _Spy(_binding._fast) if native else None
+            m.setattr(_binding, "_fast", spy)
             try:
                 fn(**args)
                 torch.cuda.synchronize()
                 out.append({k: v.cpu() for k, v in args.items() if isinstance(v, torch.Tensor)})
             except (TypeError, ValueError, _binding.ForkError) as e:
                 out.append((type(e), str(e)))
+            assert not (native and taken) or spy.returned == [_binding.FORK_OK]
     return out
 
 
@@ -83,7 +98,7 @@ def test_native_calls_match_the_bindings_own(monkeypatch, name):
     def own_stream(a):
         a["stream"] = torch.cuda.current_stream()
     for change in (lambda a: None, own_stream):
-        a, b = _both(monkeypatch, fn, kw, change)
+        a, b = _both(monkeypatch, fn, kw, change, taken=True)
         assert set(a) == set(b)
         for k in a:
             assert torch.equal(a[k].view(torch.uint8), b[k].view(torch.uint8)), k
@@ -109,7 +124,7 @@ def test_native_calls_match_the_bindings_own(monkeypatch, name):
 
 
 @pytest.mark.parametrize("name", ["step", "noalloc", "logprob"])
-def test_native_calls_take_the_lm_head_events(name):
+def test_native_calls_take_the_lm_head_events(monkeypatch, name):
     """The pair of events is recorded by the native call, around the LM head;
     a pair of another form is left to the binding."""
     fn, kw = dict(_calls())[name]
@@ -117,10 +132,15 @@ def test_native_calls_take_the_lm_head_events(name):
     for e in ev:
         e.record()
     pair = tuple(e.cuda_event for e in ev)
-    for events in (pair, list(pair)):
+    _binding.lib()
+    for events, returned in ((pair, _binding.FORK_OK), (list(pair), None)):
+        spy = _Spy(_binding._fast)
+        monkeypatch.setattr(_binding, "_fast", spy)
         begin = torch.cuda.Event(enable_timing=True)
         begin.record()
         fn(**kw, events=events)
+        monkeypatch.undo()
+        assert spy.returned == [returned]
         torch.cuda.synchronize()
         assert begin.elapsed_time(ev[0]) >= 0
         assert ev[0].elapsed_time(ev[1]) > 0
