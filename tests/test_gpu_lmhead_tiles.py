@@ -72,15 +72,17 @@ def test_drawn_candidates_of_a_ragged_tile(V, M, dtype):
 
 
 # V = 32000 (125 vocabulary tiles): 1024 rows take tiles of 256 positions, 160
-# rows tiles of 128, 40 rows tiles of 64; V = 2000 takes 64 throughout; fp32
+# rows tiles of 128, 40 rows tiles of 64; V = 2000 takes 64 throughout; V = 70000
+# (274): 40 and 64 rows tiles of 64 two to a CU, on its shorter W ring; fp32
 # tiles of 16, 32, 64 alone on a CU and 64 two to a CU, then (274 vocabulary
 # tiles) 16, 32 and 64 two to a CU
 @pytest.mark.parametrize("V,sizes,dtype", [(32000, (40, 160, 1024), torch.bfloat16),
                                            (2000, (3, 70, 300), torch.bfloat16),
+                                           (70000, (40, 64, 1024), torch.bfloat16),
                                            (32000, (16, 48, 128, 256), torch.float32),
                                            (70000, (16, 32, 300), torch.float32)])
 @pytest.mark.parametrize("temperature", [0.0, 0.8])
-@pytest.mark.parametrize("d", [32, 72])  # one stage (fp32: three tiles to a CU), and more
+@pytest.mark.parametrize("d", [32, 72, 264])  # one stage (fp32: three tiles to a CU), and more
 def test_rows_do_not_depend_on_the_tile(V, sizes, dtype, temperature, d):
     h, W = _inputs(max(sizes), d, V, V, dtype)
     outs = [_step(h[:n].contiguous(), W, temperature) for n in sizes]
@@ -110,3 +112,30 @@ def test_quartered_tail_matches_whole_tiles(M, d, V):
         part = torch.zeros_like(lp[rows])
         _binding.logprob(hd[rows].contiguous(), Wd, toks[rows].contiguous(), part)
         assert torch.equal(part.view(torch.int32), lp[rows].view(torch.int32)), rows
+
+
+@pytest.mark.parametrize("B,BL,d,V", [(206, 5, 40, 13300), (43, 21, 72, 50257)])
+def test_quartered_tail_through_a_row_list(B, BL, d, V):
+    """The same tiles with the positions gathered: the active blocks, greedy and
+    drawn, and given rows' likelihoods, against the same rows without a list."""
+    L, tau = 2 * BL, 0.9
+    h, W = _inputs(B * L, d, V, B)
+    hd, Wd = h.to(DEV), W.to(DEV)
+    rng = np.random.default_rng(B)
+    bs = rng.integers(0, 2, B) * BL
+    mask = np.ones(B * L, np.uint8)
+    mask.reshape(B, L)[5] = 0                              # no rows of this sequence
+    rows = (np.arange(B)[:, None] * L + bs[:, None] + np.arange(BL))[np.arange(B) != 5].ravel()
+    for temperature in (0.0, 0.8):
+        out = [gpu_step(hd, Wd, np.full(B * L, -1), mask, bs, B, L, BL, tau, rows_mode=mode,
+                        temperature=temperature, seed=11, counter=2)
+               for mode in (_binding.FORK_ROWS_ACTIVE, _binding.FORK_ROWS_ALL)]
+        for k in ("conf", "entropy", "logp", "lse", "argmax"):
+            a, b = (getattr(g, k)[rows] for g in out)
+            assert np.array_equal(a.view(np.int32), b.view(np.int32)), (k, temperature)
+    pick = torch.as_tensor(rng.permutation(B * L)[:B * BL].astype(np.int32)).to(DEV)
+    toks = torch.as_tensor(rng.integers(0, V, B * BL).astype(np.int32)).to(DEV)
+    a, b = torch.zeros(B * BL, device=DEV), torch.zeros(B * BL, device=DEV)
+    _binding.logprob(hd, Wd, toks, a, rows=pick)
+    _binding.logprob(hd[pick.long()].contiguous(), Wd, toks, b)
+    assert torch.equal(a.view(torch.int32), b.view(torch.int32))
