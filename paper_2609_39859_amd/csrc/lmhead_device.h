@@ -30,9 +30,6 @@ constexpr int kBufferWord3 = 0x00020000;
 constexpr unsigned kOutOfRange = 0x80000000u;
 
 __device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
-__device__ __forceinline__ int lds_off(int row, int chunk) {
-  return row * kSlab + ((chunk ^ swz(row)) << 4);
-}
 
 // Workgroup id `bid` of `n` in the order of its XCD: workgroups are dealt to the
 // XCDs round-robin (XCD x gets x, x + 8, ...), each takes a contiguous range.
