@@ -17,16 +17,17 @@
 //     anyway: 6.8 instead of 6.3 TB/s on a load-only kernel of this access
 //     pattern.  (A W that fits is better cached: with one 130 MB W read by
 //     every step 37 us cached, 51 us nontemporal.)
-// Measured, LM head alone, 256-position kernel -> this one (us):
-//   M = 32,  d = 4096, V = 126464: 178 -> 153 (6.8 TB/s); M = 128: 185 -> 169;
-//   M = 256: 256 -> 223; M = 256, V = 15808: 79 -> 56; M = 128, V = 2000:
-//   52 -> 36; M = 128, d = 1024, V = 32000: 24.7 -> 19.9; d = 256, V = 2000:
-//   14 -> 9.
+// Measured, likelihoods of M rows (LM head and merge, us, replayed as a graph),
+// 256-position kernel -> this one: d = 4096, V = 126464: M = 32 189 -> 165, 64 231
+// -> 203, 128 200 -> 178, 256 250 -> 231; d = 4096: M = 256, V = 15808 79 -> 47, M =
+// 128, V = 2000 54 -> 38; M = 128: d = 1024, V = 32000 26 -> 21, d = 256, V = 2000
+// 17 -> 10.
 // With more than one round of 64-position tiles a two-slot W ring (80 KiB) puts
 // two workgroups on a CU, so that one's statistics and first loads run under the
-// other's main loop (M = 64, V = 83339, d = 224 / 1024 / 4096: 17.3 / 43.8 / 156
-// -> 15.6 / 39.5 / 143 us); with one round the third slot is worth more (M = 130,
-// V = 9000, d = 4096: 38 against 56 us).
+// other's main loop (the same measure, M = 64, V = 83339, d = 224 / 1024 / 4096:
+// 20.0 / 39.3 / 151 -> 18.2 / 35.7 / 140; V = 126464, d = 4096, where W streams at
+// the read rate, 205 -> 204); with one round the third slot is worth more (M =
+// 130, V = 9000, d = 4096: 41 against 58).
 // Tried and not kept: 128 vocabulary rows per workgroup with two workgroups
 // per CU (equal when W streams, slower otherwise: twice the hidden traffic),
 // four W slots instead of three (equal), loads of W and hidden issued by
