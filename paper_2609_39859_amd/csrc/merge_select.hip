@@ -562,9 +562,9 @@ __device__ __forceinline__ int bit_count(uint64_t m) { return (int)__popcll(m); 
 // call, together with it): one lane per sequence position by position or, for
 // aligned blocks of at most 32, with wide loads / 32 or 64 positions by four or
 // eight lanes whatever the block / now.  2^20 sequences x blocks of 1: 12.5 / 58 /
-// 11; of 4 33 / 62 / 19; 131072 x 8 17 / 15 / 11; x 32, rows of 32 14.2 / 16.5 /
-// 12.0; rows of 101 78 / 23 / 20; 131072 x 64 130 / 24 / 25; highest entropy,
-// 131072 x 32 68 / 16 / 14.  Slower than one lane: leftmost or random picks of
+// 9.3; of 4 33 / 62 / 19; 131072 x 8 12.7 / 11.8 / 6.9; x 32, rows of 32 14.2 /
+// 16.5 / 12.0; rows of 101 78 / 25 / 20; 131072 x 64 128 / 23 / 19; highest
+// entropy, 131072 x 32 68 / 16 / 14.  Slower than one lane: leftmost or random picks of
 // 131072 sequences in rows of 96, 16.0 against 17.2.
 // Lane t of a group holds positions 4 G q + 4 t + {0..3} of the block, in bits of
 // the same numbers.
