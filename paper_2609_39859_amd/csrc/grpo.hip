@@ -56,7 +56,7 @@ __global__ __launch_bounds__(64 * kWaves) void grpo_group_kernel(
     float* __restrict__ rollout_obj, float* __restrict__ group_obj,
     uint8_t* __restrict__ skipped) {
   __shared__ float red[kWaves];
-  __shared__ int differ[kWaves];
+  __shared__ float2 first[kWaves];  // sum of the rewards, whether they differ
   __shared__ float ro[kMaxGroupSize];
   const int g = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -81,16 +81,22 @@ __global__ __launch_bounds__(64 * kWaves) void grpo_group_kernel(
     s += r[j];
     equal &= r[j] == r0;
   }
+  s = wave_sum(s);
   const unsigned long long unequal = __ballot(!equal);
-  if (lane == 0) differ[w] = unequal != 0;
-  const float mean = block_sum<kWaves>(s, red) / (float)G;
+  if (lane == 0) first[w] = make_float2(s, unequal ? 1.f : 0.f);
+  __syncthreads();
+  float sum = 0.f, any = 0.f;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) {
+    const float2 f = first[k];
+    sum += f.x;
+    any += f.y;
+  }
+  const float mean = sum / (float)G;
   float q = 0.f;
   for (int j = tid; j < G; j += 64 * kWaves) q += (r[j] - mean) * (r[j] - mean);
   const float sd = sqrtf(block_sum<kWaves>(q, red) / (float)G);
-  int any = 0;
-#pragma unroll
-  for (int k = 0; k < kWaves; ++k) any |= differ[k];
-  const bool skip = !(sd > 0.f) || !any;
+  const bool skip = !(sd > 0.f) || any == 0.f;
 
   // one wave per rollout, lanes over its entries
   for (int j = w; j < G; j += kWaves) {
